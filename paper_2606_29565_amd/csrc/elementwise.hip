@@ -9,6 +9,7 @@
 // input, plus the sums of squares of x over 1024-column blocks.  The kernel that consumes
 // the projection's split sums (QKV epilogue, SwiGLU) multiplies them by inv.  No kernel
 // has to see a whole row at once, so the row kernels spread over (row, block) grids.
+#include <algorithm>
 #include <cmath>
 
 #include "common.hpp"
@@ -248,21 +249,60 @@ __global__ __launch_bounds__(256) void final_norm_rows_kernel(Shape s, StepView 
 // Sliding-window shift (Sec. 3.6, a mutation that relocates positions): the committed
 // cells [delta, delta + n_new) of every layer move down to [0, n_new).  RoPE turns the
 // key of position p by the angles p * theta_i, so a key moving from p to p - delta is
-// turned back by delta * theta_i; values move unchanged.  One workgroup per (kv head,
-// layer, K or V) moves its cells in ascending chunks: every source of a chunk is read
-// (and the reads completed) before the workgroup's barrier, and only then is any cell of
-// the chunk written, so the in-place move never reads a cell it already overwrote (later
-// chunks read only cells above this chunk's destinations).
-template <typename T>
-__global__ __launch_bounds__(256) void shift_kernel(Shape s, void* kv, int64_t cap, int n_new,
-                                                    int delta) {
-  constexpr int CH = 64;  // cells per chunk
-  __shared__ float2 rot[128];  // (cos, sin) of -delta * theta_i, i < dh / 2
-  const int c = blockIdx.x, layer = blockIdx.y, which = blockIdx.z;
+// turned back by delta * theta_i; values move unchanged.
+//
+// Bound by memory (one read and one write of every surviving cell), so what matters is
+// that the in-place move is cut into enough independent pieces, each with several 16-byte
+// loads in flight per thread.  Grid (blocks, kv heads, layers), blocks [0, kblocks) for the
+// keys, the others for the values, 16 V^T rows each:
+//   * keys, CHAIN: a thread owns the cells r, r + delta, r + 2 delta, ... of one residue r and
+//     8 pairs of dims (16 bytes and the 16 bytes half a row on).  Cell t's destination is cell
+//     t - 1's source, which the same thread has loaded already, so no barrier is needed and
+//     the chains of a head are delta * dh / 16 threads;
+//   * keys, not CHAIN (too few residues for a workgroup's threads): one workgroup per head
+//     takes 8 cells per thread per trip in ascending order; its loads are complete before
+//     the trip's barrier, and later trips read only cells above the ones it wrote;
+//   * values: a wave owns a whole V^T row and moves it 8 units of 16 bytes per lane per trip.
+//     Destinations and the loads are aligned units; a shift that is no multiple of a unit
+//     takes each destination unit out of two neighbouring source units.
+// One 256-thread workgroup per (head, layer, K or V) with 2-byte accesses, as it was, shifted
+// 8192 cells of 4 layers of the 8B shape by 1024 (235 MB) in 272 us (0.86 TB/s); this takes
+// 58 us (4.05 TB/s; a plain copy of 4 GiB runs at 4.74 TB/s).
+constexpr int kShiftThreads = 1024;
+
+__device__ __forceinline__ uint4 pack_unit(const float (&f)[8], bf16_t) {
+  uint32_t w[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) w[i] = f32_to_bf16(f[2 * i]) | ((uint32_t)f32_to_bf16(f[2 * i + 1]) << 16);
+  return make_uint4(w[0], w[1], w[2], w[3]);
+}
+__device__ __forceinline__ uint4 pack_unit(const float (&f)[4], float) {
+  return make_uint4(__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]),
+                    __float_as_uint(f[3]));
+}
+
+// Dwords [D, D + 4) of the 8 dwords of two neighbouring units, or (half) the 16 bytes that
+// start 2 bytes further.
+template <int D>
+__device__ __forceinline__ uint4 funnel(const uint4& a, const uint4& b, bool half) {
+  const uint32_t d[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+  uint32_t o[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) o[i] = half ? (d[i + D] >> 16) | (d[i + D + 1] << 16) : d[i + D];
+  return make_uint4(o[0], o[1], o[2], o[3]);
+}
+
+template <typename T, bool CHAIN>
+__global__ __launch_bounds__(kShiftThreads) void shift_kernel(Shape s, void* kv, int64_t cap,
+                                                              int n_new, int delta, int kblocks) {
+  constexpr int E = Elem<T>::kPerFrag;  // elements of a 16-byte unit
+  constexpr int R = 8;                  // units in flight per thread
+  __shared__ float2 rot[64];            // (cos, sin) of -delta * theta_i, i < dh / 2 (dh <= 128)
+  const int c = blockIdx.y, layer = blockIdx.z, tid = threadIdx.x;
   const int dh = s.dh, half = dh / 2;
   T* base = static_cast<T*>(kv) + (int64_t)layer * 2 * s.n_kv * cap * dh;
-  if (which == 0) {
-    for (int i = threadIdx.x; i < half; i += 256) {
+  if ((int)blockIdx.x < kblocks) {
+    for (int i = tid; i < half; i += kShiftThreads) {
       const double th = -(double)delta * pow(s.rope_base, -2.0 * i / dh);
       double sn, cs;
       sincos(th, &sn, &cs);
@@ -270,56 +310,94 @@ __global__ __launch_bounds__(256) void shift_kernel(Shape s, void* kv, int64_t c
     }
     __syncthreads();
     T* K = base + (int64_t)c * cap * dh;
-    const int items = CH * half;  // (cell, pair) items of a chunk
-    for (int a = 0; a < n_new; a += CH) {
-      constexpr int PER = (CH * 64 + 255) / 256;  // items per thread (dh <= 128)
-      float va[PER], vb[PER];
+    const int groups = half / E;  // threads per cell
+    const int lane_cell = CHAIN ? (blockIdx.x * kShiftThreads + tid) / groups : tid / groups;
+    const int i0 = tid % groups * E;
+    float2 r[E];
 #pragma unroll
-      for (int q = 0; q < PER; ++q) {
-        const int it = threadIdx.x + q * 256;
-        const int cell = a + it / half, i = it % half;
-        const bool ok = it < items && cell < n_new;
-        const int64_t src = ((int64_t)(ok ? cell : 0) + delta) * dh + i;
-        va[q] = load_elem(K, src);
-        vb[q] = load_elem(K, src + half);
+    for (int e = 0; e < E; ++e) r[e] = rot[i0 + e];
+    // destination cells of this thread: first, first + step, ... (trips of R)
+    const int step = CHAIN ? delta : kShiftThreads / groups;
+    const int first = lane_cell;
+    if (CHAIN && (first >= delta || first >= n_new)) return;
+    const int64_t stride = (int64_t)step * dh;
+    for (int t0 = first; CHAIN ? t0 < n_new : t0 - first < n_new; t0 += R * step) {
+      uint4 va[R], vb[R];
+#pragma unroll
+      for (int u = 0; u < R; ++u) {
+        // (past the end: the last cell again, never stored)
+        const T* p = K + (int64_t)(min((int64_t)t0 + (int64_t)u * step, (int64_t)n_new - 1) + delta) * dh + i0;
+        va[u] = *reinterpret_cast<const uint4*>(p);
+        vb[u] = *reinterpret_cast<const uint4*>(p + half);
       }
-      __builtin_amdgcn_s_waitcnt(0);  // this thread's reads are complete
-      __syncthreads();                // ... and every other thread's
+      if constexpr (!CHAIN) {
+        __builtin_amdgcn_s_waitcnt(0);  // this thread's reads are complete
+        __syncthreads();                // ... and every other thread's
+      }
 #pragma unroll
-      for (int q = 0; q < PER; ++q) {
-        const int it = threadIdx.x + q * 256;
-        const int cell = a + it / half, i = it % half;
-        if (it < items && cell < n_new) {
-          const float2 r = rot[i];
-          const int64_t dst = (int64_t)cell * dh + i;
-          store_elem(K, dst, va[q] * r.x - vb[q] * r.y);
-          store_elem(K, dst + half, va[q] * r.y + vb[q] * r.x);
+      for (int u = 0; u < R; ++u) {
+        if ((int64_t)t0 + (int64_t)u * step < n_new) {
+          float a[E], b[E], x[E], y[E];
+          frag_to_f32(va[u], a);
+          frag_to_f32(vb[u], b);
+#pragma unroll
+          for (int e = 0; e < E; ++e) {
+            x[e] = a[e] * r[e].x - b[e] * r[e].y;
+            y[e] = a[e] * r[e].y + b[e] * r[e].x;
+          }
+          T* q = K + (int64_t)t0 * dh + u * stride + i0;
+          *reinterpret_cast<uint4*>(q) = pack_unit(x, T{});
+          *reinterpret_cast<uint4*>(q + half) = pack_unit(y, T{});
         }
       }
-      __syncthreads();  // the chunk's writes are issued before the next chunk's reads
     }
   } else {
-    T* Vt = base + (int64_t)s.n_kv * cap * dh + (int64_t)c * dh * cap;  // [dh][cap]
-    constexpr int CV = 256;                    // positions per chunk
-    for (int a = 0; a < n_new; a += CV) {
-      constexpr int PER = CV * 128 / 256;      // elements per thread (dh <= 128)
-      float v[PER];
+    const int lane = tid & 63;
+    const int row = (blockIdx.x - kblocks) * (kShiftThreads / 64) + (tid >> 6);
+    if (row >= dh) return;
+    T* V = base + (int64_t)s.n_kv * cap * dh + ((int64_t)c * dh + row) * cap;  // [dh][cap]
+    const uint4* src = reinterpret_cast<const uint4*>(V);
+    const int units = (n_new + E - 1) / E, last = (int)(cap / E) - 1;
+    const int du = delta / E, bytes = delta % E * Elem<T>::kBytes;
+    const bool odd = bytes & 2;
+    for (int u0 = lane; u0 - lane < units; u0 += R * 64) {
+      uint4 a[R], b[R];
 #pragma unroll
-      for (int q = 0; q < PER; ++q) {
-        const int it = threadIdx.x + q * 256;
-        const int row = it / CV, pos = a + it % CV;
-        const bool ok = row < dh && pos < n_new;
-        v[q] = load_elem(Vt, (int64_t)(ok ? row : 0) * cap + (ok ? pos : 0) + delta);
+      for (int u = 0; u < R; ++u) {
+        const int at = min(u0 + u * 64, units - 1) + du;  // holds cell 8 at + delta at most: in the row
+        a[u] = src[at];
+        b[u] = bytes ? src[min(at + 1, last)] : a[u];
       }
+      // every load of the wave's trip is complete before it overwrites a cell
       __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
-      for (int q = 0; q < PER; ++q) {
-        const int it = threadIdx.x + q * 256;
-        const int row = it / CV, pos = a + it % CV;
-        if (row < dh && pos < n_new) store_elem(Vt, (int64_t)row * cap + pos, v[q]);
+      for (int u = 0; u < R; ++u) {
+        const int at = u0 + u * 64;
+        if (at >= units) continue;
+        uint4 o;
+        switch (bytes >> 2) {
+          case 0: o = funnel<0>(a[u], b[u], odd); break;
+          case 1: o = funnel<1>(a[u], b[u], odd); break;
+          case 2: o = funnel<2>(a[u], b[u], odd); break;
+          default: o = funnel<3>(a[u], b[u], odd); break;
+        }
+        T* q = V + (int64_t)at * E;
+        const int live = n_new - at * E;
+        if (live >= E) {
+          *reinterpret_cast<uint4*>(q) = o;
+        } else {  // the cells from n_new on stay as they are
+          const uint32_t w[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+          for (int e = 0; e < E; ++e)
+            if (e < live) {
+              if constexpr (E == 8)
+                reinterpret_cast<uint16_t*>(q)[e] = (uint16_t)(w[e / 2] >> (16 * (e % 2)));
+              else
+                reinterpret_cast<uint32_t*>(q)[e] = w[e];
+            }
+        }
       }
-      __syncthreads();
     }
   }
 }
@@ -440,11 +518,21 @@ hipError_t shift_cells(const Shape& s, void* kv, int64_t cap, int n_new, int del
                        hipStream_t st) {
   if (n_new <= 0) return hipSuccess;
   if (delta < 1 || s.dh > 128 || s.dh % 2) return hipErrorInvalidValue;
-  dim3 grid(s.n_kv, s.n_layers, 2);
-  if (s.bf16)
-    SPP_LAUNCH(shift_kernel<bf16_t>, grid, dim3(256), 0, st, s, kv, cap, n_new, delta);
-  else
-    SPP_LAUNCH(shift_kernel<float>, grid, dim3(256), 0, st, s, kv, cap, n_new, delta);
+  // A thread per (residue, 16-byte pair) where that gives a head at least one workgroup of
+  // threads; with fewer residues the chains get long and thin, and one workgroup moving
+  // 8 * 1024 units per trip has as many loads in flight.
+  const int groups = s.dh / 2 / (s.bf16 ? 8 : 4);
+  const bool chain = (int64_t)delta * groups >= kShiftThreads;
+  const int kblocks = chain ? (int)(((int64_t)std::min(delta, n_new) * groups + kShiftThreads - 1) / kShiftThreads) : 1;
+  const dim3 grid(kblocks + (s.dh + kShiftThreads / 64 - 1) / (kShiftThreads / 64), s.n_kv, s.n_layers);
+#define SPP_SHIFT(T, C) \
+  SPP_LAUNCH((shift_kernel<T, C>), grid, dim3(kShiftThreads), 0, st, s, kv, cap, n_new, delta, kblocks)
+  if (s.bf16) {
+    if (chain) SPP_SHIFT(bf16_t, true); else SPP_SHIFT(bf16_t, false);
+  } else {
+    if (chain) SPP_SHIFT(float, true); else SPP_SHIFT(float, false);
+  }
+#undef SPP_SHIFT
   return hipGetLastError();
 }
 

@@ -61,6 +61,41 @@ def test_shift_moves_and_turns_the_cells_like_the_oracle(shape_name, n, delta):
     log(f"shift {shape_name} n={n} delta={delta}: cells match the oracle")
 
 
+@pytest.mark.parametrize("dtype,dh,n,delta", [
+    # keys as chains of equal residues (delta * dh / 16 >= 1024 for bf16): chains longer and
+    # shorter than one trip of 8 cells, a last workgroup with idle threads, one cell left
+    ("bf16", 64, 2600, 256), ("bf16", 64, 2600, 257), ("bf16", 64, 600, 599),
+    ("bf16", 128, 1400, 129), ("f32", 64, 1300, 131),
+    # one workgroup per head, several trips; V^T rows of more than one trip (4096 cells)
+    ("bf16", 64, 4700, 255), ("bf16", 128, 4300, 127), ("f32", 64, 2200, 3),
+    # every distance of a V^T unit's source from a 16-byte unit, and whole units
+    ("bf16", 128, 530, 2), ("bf16", 128, 530, 5), ("bf16", 128, 530, 8), ("f32", 64, 530, 4)])
+def test_shift_at_the_edges_of_its_work_split(dtype, dh, n, delta):
+    import torch
+    import paper_2606_29565_amd as spp
+    shape = synth.Shape("shiftw", 2, 256, 256 // dh, 2, dh, 512, 2048, 1e4, dtype)
+    b = build_model(shape, SEED, max_tokens=16)
+    cap = n + 24
+    sess = spp.Session(b.model, cap)
+    sess.kv.zero_()  # (the cells no one wrote are compared too)
+    fill_synthetic_kv(b, sess, 0, n)
+    sess.restore(n)
+    before = [read_kv(b, sess, l, cap) for l in range(shape.n_layers)]
+    sess.shift(delta)
+    torch.cuda.synchronize()
+    okv = _oracle_kv_after_shift(shape, SEED, n, delta, cap)
+    n_new = n - delta
+    for l in range(shape.n_layers):
+        K, V = read_kv(b, sess, l, cap)
+        Ko, Vo = okv.layer(l)
+        np.testing.assert_array_equal(V[:, :n_new], Vo[:, :n_new])
+        assert _key_close(K[:, :n_new], Ko[:, :n_new], shape.bf16), \
+            f"layer {l}: keys differ by {max_abs(K[:, :n_new], Ko[:, :n_new]):.3e}"
+        # the cells past the survivors are left as they were
+        np.testing.assert_array_equal(K[:, n_new:], before[l][0][:, n_new:])
+        np.testing.assert_array_equal(V[:, n_new:], before[l][1][:, n_new:])
+
+
 def test_shift_then_preposition_matches_the_oracle():
     import torch
     import paper_2606_29565_amd as spp
