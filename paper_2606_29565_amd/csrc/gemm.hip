@@ -30,13 +30,7 @@
 //     its waves alternate between 16-column blocks of the gate and of the up matrix at
 //     the same columns, the up wave hands its accumulators to the gate wave through LDS,
 //     and the gate wave writes silu(inv*gate) * (inv*up) as the down projection's input
-//     (inv = the row's 1/RMS of the factored RMSNorm);
-//   * MXFP4 weights (Q4: 4-bit e2m1 codes and one e8m0 scale per 32 along K, tiled by
-//     pack_weight_fp4) go through the same pipeline: a step is 128 elements (a 1 KB code
-//     block and a 64-byte scale block per 16 columns), dequantized exactly to bf16 in
-//     registers (gfx950's scaled fp4 conversion) into the four B fragments of the step.
-//     A 4-bit byte feeds four times the products of a bf16 one, so each wave takes
-//     several column blocks and every A fragment read from LDS serves all of them.
+//     (inv = the row's 1/RMS of the factored RMSNorm).
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -44,8 +38,6 @@ namespace spp {
 namespace {
 
 constexpr int kStepBytes = 128;  // bytes of one weight row per step (8 units of 16 B)
-constexpr int kQ4Step = 128;     // elements per step of an MXFP4 matrix
-constexpr int kQ4CodeBlock = 1024, kQ4ScaleBlock = 64;  // bytes per 16 rows x step
 
 // Padding of each staged activation row in LDS (bytes).  The A fragments are 16-byte
 // reads of 16 rows x 64 bytes; measured on gfx950, they run at the full LDS rate when
@@ -58,10 +50,10 @@ constexpr int kQ4CodeBlock = 1024, kQ4ScaleBlock = 64;  // bytes per 16 rows x s
 #define SPP_GEMM_BIG_WPE 2
 #endif
 
-template <typename T, bool Q4, int STEPS, int NW, int MT, int CB>
+template <typename T, int STEPS, int NW, int MT, int CB>
 struct GemmCfg {
   static constexpr int EB = Elem<T>::kBytes;
-  static constexpr int ABYTES = Q4 ? kQ4Step * EB : kStepBytes;    // activation bytes per row per step
+  static constexpr int ABYTES = kStepBytes;                        // activation bytes per row per step
   static constexpr int KSTEP = ABYTES / EB;                        // elements per step
   static constexpr int KS = STEPS * KSTEP;                         // elements per slice
   static constexpr int PITCH = STEPS * ABYTES + SPP_GEMM_PAD;      // LDS bytes per row
@@ -127,115 +119,52 @@ struct SwigluOut {
 };
 
 // One wave's column block: the lane's base addresses inside the matrix that holds it
-// (weights or codes; MXFP4 scales), the block index in that matrix and its block map.
+// and the block index in that matrix and its block map.
 struct ColBlock {
   const char* wlane;
-  const char* slane;
   int cb;
   BlockMap bm;
 };
 
-// Weights of one slice in registers.  Dtype: fragment (c, step s, half j) of lane l is
-// 16 bytes at block(ks + s) + j*1024 + l*16 of column block c.  MXFP4: lane l's 16 code
-// bytes at block(ks + s) * 1024 + l*16 and the four scales of its row at
-// block(ks + s) * 64 + (l % 16) * 4.
-template <bool Q4, int CB, int STEPS>
+// Weights of one slice in registers: fragment (c, step s, half j) of lane l is 16 bytes at
+// block(ks + s) + j*1024 + l*16 of column block c.
+template <int CB, int STEPS>
 struct WTile {
   uint4 f[CB][STEPS][2];
 };
-template <int CB, int STEPS>
-struct WTile<true, CB, STEPS> {
-  uint4 code[CB][STEPS];
-  uint32_t scale[CB][STEPS];
-};
 
-template <bool Q4, int STEPS, int CB>
-__device__ __forceinline__ void load_w(WTile<Q4, CB, STEPS>& w, const ColBlock (&cbk)[CB], int ks) {
+template <int STEPS, int CB>
+__device__ __forceinline__ void load_w(WTile<CB, STEPS>& w, const ColBlock (&cbk)[CB], int ks) {
 #pragma unroll
   for (int c = 0; c < CB; ++c)
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) {
       const int64_t b = cbk[c].bm.at(cbk[c].cb, ks + s);
-      if constexpr (Q4) {
-        w.code[c][s] = ld_global(cbk[c].wlane + b * kQ4CodeBlock);
-        w.scale[c][s] = ld_global_u32(cbk[c].slane + b * kQ4ScaleBlock);
-      } else {
-        const char* p = cbk[c].wlane + b * 2048;
-        w.f[c][s][0] = ld_global(p);
-        w.f[c][s][1] = ld_global(p + 1024);
-      }
-    }
-}
-
-// e8m0 byte J of `s` as an fp32 power of two (2^(E-127); E in [1, 254])
-template <int J>
-__device__ __forceinline__ float e8m0(uint32_t s) {
-  return __uint_as_float(((s >> (8 * J)) & 0xFFu) << 23);
-}
-
-// B fragment (8 bf16 weights: k = 32 J + 8 g + 0..7 of the step) from the code dword J
-// and the scale of that 32-element chunk; every e2m1 value times a power of two in
-// range is exact in bf16
-template <int J>
-__device__ __forceinline__ uint4 dequant_chunk(uint32_t codes, uint32_t scales) {
-  const float sc = e8m0<J>(scales);
-  return make_uint4(
-      __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(codes, sc, 0)),
-      __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(codes, sc, 1)),
-      __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(codes, sc, 2)),
-      __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(codes, sc, 3)));
-}
-
-template <int J>
-__device__ __forceinline__ uint32_t dword(const uint4& v) {
-  return J == 0 ? v.x : (J == 1 ? v.y : (J == 2 ? v.z : v.w));
-}
-
-// One 32-element chunk J of step s of an MXFP4 slice: the CB column blocks' B fragments,
-// then every part and 16-row tile reads its A fragment once for all of them.
-template <typename C, int J, int STEPS, int MT, int CB>
-__device__ __forceinline__ void mma_chunk_q4(const char* buf, const WTile<true, CB, STEPS>& w, int s,
-                                             int cl, int g, f32x4 (&acc)[C::NA][MT][CB]) {
-  uint4 b[CB];
-#pragma unroll
-  for (int c = 0; c < CB; ++c) b[c] = dequant_chunk<J>(dword<J>(w.code[c][s]), w.scale[c][s]);
-#pragma unroll
-  for (int p = 0; p < C::NP; ++p)
-#pragma unroll
-    for (int t = 0; t < MT; ++t) {
-      const uint4 a = *reinterpret_cast<const uint4*>(buf + (p * C::ROWS + t * 16 + cl) * C::PITCH +
-                                                      s * C::ABYTES + J * 64 + g * 16);
-#pragma unroll
-      for (int c = 0; c < CB; ++c) acc[p % C::NA][t][c] = mma_frag(a, b[c], acc[p % C::NA][t][c], bf16_t{});
+      const char* p = cbk[c].wlane + b * 2048;
+      w.f[c][s][0] = ld_global(p);
+      w.f[c][s][1] = ld_global(p + 1024);
     }
 }
 
 // Lane (row cl, group g) of each 16-row tile: A fragment (s, j) = row elements
 // [s*KSTEP + j*4E + g*E, +E), matching the weight fragment's reduction indices.
-template <typename T, typename C, bool Q4, int STEPS, int MT, int CB>
-__device__ __forceinline__ void mma_slice(const char* buf, const WTile<Q4, CB, STEPS>& w, int cl, int g,
+template <typename T, typename C, int STEPS, int MT, int CB>
+__device__ __forceinline__ void mma_slice(const char* buf, const WTile<CB, STEPS>& w, int cl, int g,
                                           f32x4 (&acc)[C::NA][MT][CB]) {
 #pragma unroll
   for (int s = 0; s < STEPS; ++s) {
-    if constexpr (Q4) {
-      mma_chunk_q4<C, 0>(buf, w, s, cl, g, acc);
-      mma_chunk_q4<C, 1>(buf, w, s, cl, g, acc);
-      mma_chunk_q4<C, 2>(buf, w, s, cl, g, acc);
-      mma_chunk_q4<C, 3>(buf, w, s, cl, g, acc);
-    } else {
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int p = 0; p < C::NP; ++p)
+      for (int p = 0; p < C::NP; ++p)
 #pragma unroll
-          for (int t = 0; t < MT; ++t) {
-            const uint4 a = *reinterpret_cast<const uint4*>(buf + (p * C::ROWS + t * 16 + cl) * C::PITCH +
-                                                            g * 16 + s * kStepBytes + j * 64);
+        for (int t = 0; t < MT; ++t) {
+          const uint4 a = *reinterpret_cast<const uint4*>(buf + (p * C::ROWS + t * 16 + cl) * C::PITCH +
+                                                          g * 16 + s * kStepBytes + j * 64);
 #pragma unroll
-            for (int c = 0; c < CB; ++c)
-              acc[p % C::NA][t][c] = mma_frag(a, w.f[c][s][j], acc[p % C::NA][t][c], T{});
-          }
-    }
+          for (int c = 0; c < CB; ++c)
+            acc[p % C::NA][t][c] = mma_frag(a, w.f[c][s][j], acc[p % C::NA][t][c], T{});
+        }
   }
 }
 
@@ -246,20 +175,19 @@ template <int MT, int CB>
 constexpr int gemm_waves_per_eu() { return MT == 4 && CB == 4 ? SPP_GEMM_BIG_WPE : 1; }
 // The fused gate/up of more than 8 waves per workgroup: at most 128 registers, so that its
 // 10-16 waves (3-4 per SIMD) fit one workgroup per CU.
-template <int NW, int MT, int CB, bool SW, bool Q4>
+template <int NW, int MT, int CB, bool SW>
 constexpr int gemm_kernel_waves_per_eu() {
-  return SW && !Q4 && NW > 8 ? 4 : gemm_waves_per_eu<MT, CB>();
+  return SW && NW > 8 ? 4 : gemm_waves_per_eu<MT, CB>();
 }
 
-template <typename T, bool Q4, int STEPS, int NW, int MT, int CB, bool SW>
+template <typename T, int STEPS, int NW, int MT, int CB, bool SW>
 __global__ __launch_bounds__(64 * NW)
-__attribute__((amdgpu_waves_per_eu(gemm_kernel_waves_per_eu<NW, MT, CB, SW, Q4>()))) void gemm_kernel(const T* __restrict__ X,
+__attribute__((amdgpu_waves_per_eu(gemm_kernel_waves_per_eu<NW, MT, CB, SW>()))) void gemm_kernel(const T* __restrict__ X,
                                                        const T* __restrict__ Xlo, int M, int K,
                                                        WeightCat w, int N, int iters,
                                                        float* __restrict__ P, SwigluOut so,
                                                        int row_tiles, int splits, int groups) {
-  using C = GemmCfg<T, Q4, STEPS, NW, MT, CB>;
-  static_assert(!Q4 || C::EB == 2, "MXFP4 weights multiply bf16 activations");
+  using C = GemmCfg<T, STEPS, NW, MT, CB>;
   // two activation stages (the fused SwiGLU's exchange of the up sums reuses them)
   constexpr int XCH = SW ? NW / 2 * CB * MT * 4 * 64 * 4 : 0;
   constexpr int STAGE = C::NP * C::ROWS * C::PITCH > (XCH + 1) / 2 ? C::NP * C::ROWS * C::PITCH
@@ -311,7 +239,6 @@ __attribute__((amdgpu_waves_per_eu(gemm_kernel_waves_per_eu<NW, MT, CB, SW, Q4>(
       ok[c] = fb * 16 < w.nbeg[1];
       const int mi = (wave & 1) && ok[c] ? 1 : 0;
       cbk[c].wlane = static_cast<const char*>(mi ? w.mat[1] : w.mat[0]) + lane * 16;
-      cbk[c].slane = Q4 ? static_cast<const char*>(mi ? w.scale[1] : w.scale[0]) + cl * 4 : nullptr;
       cbk[c].cb = ok[c] ? fb : 0;
       cbk[c].bm = BlockMap{w.slab, ksteps / w.slab, w.nbeg[1] / 16};
     } else {
@@ -319,11 +246,9 @@ __attribute__((amdgpu_waves_per_eu(gemm_kernel_waves_per_eu<NW, MT, CB, SW, Q4>(
       const int nn = ok[c] ? n0[c] : 0;
       const int mi = nn >= w.nbeg[2] ? 2 : (nn >= w.nbeg[1] ? 1 : 0);
       const void* mat = mi == 2 ? w.mat[2] : (mi == 1 ? w.mat[1] : w.mat[0]);
-      const void* scl = mi == 2 ? w.scale[2] : (mi == 1 ? w.scale[1] : w.scale[0]);
       const int nb = mi == 2 ? w.nbeg[2] : (mi == 1 ? w.nbeg[1] : w.nbeg[0]);
       const int ne = mi == 2 ? w.nbeg[3] : (mi == 1 ? w.nbeg[2] : w.nbeg[1]);
       cbk[c].wlane = static_cast<const char*>(mat) + lane * 16;
-      cbk[c].slane = Q4 ? static_cast<const char*>(scl) + cl * 4 : nullptr;
       cbk[c].cb = (nn - nb) / 16;
       cbk[c].bm = BlockMap{w.slab, ksteps / w.slab, (ne - nb) / 16};
     }
@@ -345,29 +270,25 @@ __attribute__((amdgpu_waves_per_eu(gemm_kernel_waves_per_eu<NW, MT, CB, SW, Q4>(
       for (int t = 0; t < MT; ++t)
 #pragma unroll
         for (int c = 0; c < CB; ++c) acc[a][t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    WTile<Q4, CB, STEPS> w0, w1;
+    WTile<CB, STEPS> w0, w1;
     uint4 ar[C::NP * C::AU];
     load_a<C>(ar, X, Xlo, M, K, r0, kbeg);
-    load_w<Q4, STEPS, CB>(w0, cbk, ks0);
+    load_w<STEPS, CB>(w0, cbk, ks0);
     store_a<C>(lds[0], ar);
     if constexpr (SW) {  // (visible after the first barrier below)
       if (r0 == rbeg && tid < (rend - rbeg) * so.nb) sm_ss[tid] = ssv;
     }
     int i = 0;
     // steady state, two slices per trip: every load is unconditional
-    // (with MXFP4 weights, scheduling barriers keep each slice's loads ahead of the
-    // previous slice's products; the scheduler would otherwise sink them to their use)
     for (; i + 2 < iters; i += 2) {
       __syncthreads();  // lds[0] holds slice i; lds[1] is free
       load_a<C>(ar, X, Xlo, M, K, r0, kbeg + (i + 1) * C::KS);
-      load_w<Q4, STEPS, CB>(w1, cbk, ks0 + (i + 1) * STEPS);
-      if constexpr (Q4) __builtin_amdgcn_sched_barrier(0);
+      load_w<STEPS, CB>(w1, cbk, ks0 + (i + 1) * STEPS);
       mma_slice<T, C>(lds[0], w0, cl, g, acc);
       store_a<C>(lds[1], ar);
       __syncthreads();  // lds[1] holds slice i+1; lds[0] is free
       load_a<C>(ar, X, Xlo, M, K, r0, kbeg + (i + 2) * C::KS);
-      load_w<Q4, STEPS, CB>(w0, cbk, ks0 + (i + 2) * STEPS);
-      if constexpr (Q4) __builtin_amdgcn_sched_barrier(0);
+      load_w<STEPS, CB>(w0, cbk, ks0 + (i + 2) * STEPS);
       mma_slice<T, C>(lds[1], w1, cl, g, acc);
       store_a<C>(lds[0], ar);
     }
@@ -375,8 +296,7 @@ __attribute__((amdgpu_waves_per_eu(gemm_kernel_waves_per_eu<NW, MT, CB, SW, Q4>(
     __syncthreads();
     if (i + 1 < iters) {
       load_a<C>(ar, X, Xlo, M, K, r0, kbeg + (i + 1) * C::KS);
-      load_w<Q4, STEPS, CB>(w1, cbk, ks0 + (i + 1) * STEPS);
-      if constexpr (Q4) __builtin_amdgcn_sched_barrier(0);
+      load_w<STEPS, CB>(w1, cbk, ks0 + (i + 1) * STEPS);
       mma_slice<T, C>(lds[0], w0, cl, g, acc);
       store_a<C>(lds[1], ar);
       __syncthreads();
@@ -470,10 +390,10 @@ __global__ __launch_bounds__(256) void pack_kernel(const uint4* __restrict__ src
   }
 }
 
-template <typename T, bool Q4, int STEPS, int NW, int MT, int CB, bool SW>
+template <typename T, int STEPS, int NW, int MT, int CB, bool SW>
 hipError_t launch_t(const void* X, const void* Xlo, int M, int K, const WeightCat& w, int N,
                     int iters, int row_tiles, float* P, const SwigluOut& so, hipStream_t s) {
-  using C = GemmCfg<T, Q4, STEPS, NW, MT, CB>;
+  using C = GemmCfg<T, STEPS, NW, MT, CB>;
   const int splits = K / (C::KS * iters), groups = (N + 16 * NW * CB - 1) / (16 * NW * CB);
   // row tiles: one tile of C::ROWS rows per workgroup (and, fused, its rows' sums of
   // squares staged one per thread)
@@ -482,15 +402,14 @@ hipError_t launch_t(const void* X, const void* Xlo, int M, int K, const WeightCa
     return hipErrorInvalidValue;
   const dim3 grid = row_tiles > 0 ? dim3((splits * groups + 7) / 8 * 8 * row_tiles, 1)
                                    : dim3(splits, groups);
-  SPP_LAUNCH((gemm_kernel<T, Q4, STEPS, NW, MT, CB, SW>), grid, dim3(64 * NW), 0, s,
+  SPP_LAUNCH((gemm_kernel<T, STEPS, NW, MT, CB, SW>), grid, dim3(64 * NW), 0, s,
                      static_cast<const T*>(X), static_cast<const T*>(Xlo), M, K, w, N, iters, P,
                      so, row_tiles, splits, groups);
   return hipGetLastError();
 }
 
 // The instantiated launch shapes (waves, 16-row tiles, column blocks per wave, steps per
-// slice): those the plans below pick, for dtype and MXFP4 weights, with and without the
-// fused SwiGLU.
+// slice): those the plans below pick, with and without the fused SwiGLU.
 #ifndef SPP_GEMM_SHAPES
 #define SPP_GEMM_SHAPES(X) \
   X(16, 1, 1, 2) X(16, 1, 1, 4) X(16, 2, 1, 2) X(16, 2, 1, 4) X(16, 4, 1, 2) X(16, 4, 1, 4) \
@@ -507,25 +426,14 @@ hipError_t launch_t(const void* X, const void* Xlo, int M, int K, const WeightCa
   X(16, 1, 1, 2) X(16, 2, 1, 2) \
   X(4, 4, 4, 1)
 #endif
-#ifndef SPP_GEMM_Q4_SHAPES
-#define SPP_GEMM_Q4_SHAPES(X) X(8, 1, 2, 1) X(8, 2, 2, 1) X(8, 4, 2, 1) X(8, 8, 2, 1) X(8, 2, 4, 1)
-#endif
-#ifndef SPP_GEMM_Q4_SWIGLU_SHAPES
-#define SPP_GEMM_Q4_SWIGLU_SHAPES(X) X(8, 1, 2, 1) X(8, 2, 2, 1) X(8, 4, 2, 1)
-#endif
-
-template <typename T, bool Q4, bool SW>
+template <typename T, bool SW>
 hipError_t launch(const k::GemmPlan& p, const void* X, const void* Xlo, int M, int K,
                   const WeightCat& w, int N, float* P, const SwigluOut& so, hipStream_t s) {
 #define SPP_GEMM_TRY(nw_, mt_, cb_, st_)                                                    \
   if (p.nw == nw_ && p.mt == mt_ && p.cb == cb_ && p.steps == st_)                          \
-    return launch_t<T, Q4, st_, nw_, mt_, cb_, SW>(X, Xlo, M, K, w, N, p.iters, p.row_tiles, P, \
+    return launch_t<T, st_, nw_, mt_, cb_, SW>(X, Xlo, M, K, w, N, p.iters, p.row_tiles, P, \
                                                    so, s);
-  if constexpr (Q4 && SW) {
-    SPP_GEMM_Q4_SWIGLU_SHAPES(SPP_GEMM_TRY)
-  } else if constexpr (Q4) {
-    SPP_GEMM_Q4_SHAPES(SPP_GEMM_TRY)
-  } else if constexpr (SW) {
+  if constexpr (SW) {
     SPP_GEMM_SWIGLU_SHAPES(SPP_GEMM_TRY)
   } else {
     SPP_GEMM_SHAPES(SPP_GEMM_TRY)
@@ -664,8 +572,8 @@ hipError_t gemm(const Shape& s, const GemmPlan& p, const void* X, const void* Xl
   if (M <= 0 || p.iters < 1 || (s.bf16 && !Xlo) || w.slab < 1 || (K * (s.bf16 ? 2 : 4) / kStepBytes) % w.slab)
     return hipErrorInvalidValue;
   const SwigluOut none{};
-  return s.bf16 ? launch<bf16_t, false, false>(p, X, Xlo, M, K, w, N, partials, none, st)
-                : launch<float, false, false>(p, X, Xlo, M, K, w, N, partials, none, st);
+  return s.bf16 ? launch<bf16_t, false>(p, X, Xlo, M, K, w, N, partials, none, st)
+                : launch<float, false>(p, X, Xlo, M, K, w, N, partials, none, st);
 }
 
 // The fused gate/up + SwiGLU projection (no K-splits): 8-wave workgroups of four gate/up
@@ -723,8 +631,8 @@ hipError_t gemm_swiglu(const Shape& s, const GemmPlan& p, const void* X, const v
       (K * (s.bf16 ? 2 : 4) / kStepBytes) % w.slab || w.nbeg[1] != F || w.nbeg[2] != 2 * F)
     return hipErrorInvalidValue;
   const SwigluOut so{ss, res_blocks(s), s.d, s.eps, act, act_lo, F};
-  return s.bf16 ? launch<bf16_t, false, true>(p, X, Xlo, M, K, w, 2 * F, nullptr, so, st)
-                : launch<float, false, true>(p, X, Xlo, M, K, w, 2 * F, nullptr, so, st);
+  return s.bf16 ? launch<bf16_t, true>(p, X, Xlo, M, K, w, 2 * F, nullptr, so, st)
+                : launch<float, true>(p, X, Xlo, M, K, w, 2 * F, nullptr, so, st);
 }
 
 int pack_slab_steps_gateup(const Shape& s, int F, int K) {
@@ -735,87 +643,6 @@ int pack_slab_steps_gateup(const Shape& s, int F, int K) {
 int pack_slab_steps(const Shape& s, int N, int K) {
   const GemmPlan p = gemm_plan(s, 32, N, K);
   return p.steps * p.iters;
-}
-
-// MXFP4 launch shape (K-steps of 128 elements), from sweeps at the 70B projection sizes:
-// 8-wave workgroups of two column blocks per wave (one A fragment from LDS feeds both,
-// which halves the LDS reads per weight byte: with a 4-bit weight feeding four times the
-// products of a bf16 one, those reads and the matrix cores, not HBM, bound the kernel),
-// 1-step slices; the fewest K-splits whose grid fills the chip once, with at least two
-// slices each (the fp32 partials weigh more against 4-bit weights than against bf16).
-// The wide MLP gate/up at 17-32 rows (N >= 32768, run unfused: see gemm_plan_swiglu_fp4)
-// takes four column blocks per wave instead, so each A fragment feeds four products, with
-// the most K-splits that keep the grid within one round (the 70B MLP: 2 splits, 224
-// workgroups): 79.7-81.7 -> 68.8-69.4 µs plus a 5.5 µs SwiGLU against the fused kernel.
-// Four blocks for the other 70B projections measured no better (QKV, down) or slower (O).
-GemmPlan gemm_plan_fp4(const Shape& s, int M, int N, int K) {
-  (void)s;
-  GemmPlan p{};
-  const int ksteps = K / kQ4Step;
-  p.mt = M <= 16 ? 1 : (M <= 32 ? 2 : (M <= 64 ? 4 : 8));
-  const bool wide = N >= 32768 && p.mt == 2;
-  p.nw = 8;
-  p.cb = wide ? 4 : 2;
-  p.steps = 1;
-  const int slices = ksteps / p.steps;
-  const int groups = (N + 16 * p.nw * p.cb - 1) / (16 * p.nw * p.cb);
-  int best = 1;
-  for (int sp = 1; sp <= slices; ++sp) {
-    if (slices % sp || (sp > 1 && slices / sp < 2)) continue;
-    if (wide && sp > 1 && sp * groups > 256) break;
-    best = sp;
-    if (sp * groups >= 256) break;
-  }
-  p.splits = best;
-  p.iters = slices / best;
-  return p;
-}
-
-int pack_slab_steps_fp4(const Shape& s, int N, int K) {
-  const GemmPlan p = gemm_plan_fp4(s, 32, N, K);
-  return p.steps * p.iters;
-}
-
-hipError_t gemm_fp4(const Shape& s, const GemmPlan& p, const void* X, const void* Xlo, int M, int K,
-                    const WeightCat& w, int N, float* partials, hipStream_t st) {
-  if (M <= 0 || p.iters < 1 || !s.bf16 || !Xlo || w.slab < 1 || K % kQ4Step ||
-      (K / kQ4Step) % w.slab || (K / kQ4Step) % (p.steps * p.iters))
-    return hipErrorInvalidValue;
-  const SwigluOut none{};
-  return launch<bf16_t, true, false>(p, X, Xlo, M, K, w, N, partials, none, st);
-}
-
-// Fused gate/up + SwiGLU over MXFP4 weights: 8-wave workgroups of two column blocks per
-// wave (four gate/up pairs of two blocks: 128 output columns) over the full K; up to 64
-// rows (F / 128 workgroups: 224 for F = 28672).  splits = 0 where it does not apply.
-GemmPlan gemm_plan_swiglu_fp4(const Shape& s, int M, int F, int K) {
-  GemmPlan p{};
-  const int ksteps = K / kQ4Step;
-  if (!s.bf16 || M > 64 || F % 16 || K % kQ4Step || M * res_blocks(s) > 512) return p;
-  // 17-32 rows of a wide MLP: unfused, with four column blocks per wave (gemm_plan_fp4)
-  if (M > 16 && M <= 32 && 2 * F >= 32768) return p;
-  p.mt = M <= 16 ? 1 : (M <= 32 ? 2 : 4);
-  p.nw = 8;
-  p.cb = 2;
-  p.steps = 1;
-  p.iters = ksteps / p.steps;
-  p.splits = 1;
-  return p;
-}
-
-hipError_t gemm_swiglu_fp4(const Shape& s, const GemmPlan& p, const void* X, const void* Xlo, int M,
-                           int K, const WeightCat& w, int F, const float* ss, void* act,
-                           void* act_lo, hipStream_t st) {
-  if (M <= 0 || p.splits != 1 || p.iters < 1 || !s.bf16 || !Xlo || w.slab < 1 || K % kQ4Step ||
-      (K / kQ4Step) % w.slab || w.nbeg[1] != F || w.nbeg[2] != 2 * F)
-    return hipErrorInvalidValue;
-  const SwigluOut so{ss, res_blocks(s), s.d, s.eps, act, act_lo, F};
-  return launch<bf16_t, true, true>(p, X, Xlo, M, K, w, 2 * F, nullptr, so, st);
-}
-
-int pack_slab_steps_gateup_fp4(const Shape& s, int F, int K) {
-  const GemmPlan p = gemm_plan_swiglu_fp4(s, 32, F, K);
-  return p.splits == 1 ? p.steps * p.iters : pack_slab_steps_fp4(s, 2 * F, K);
 }
 
 hipError_t pack_weight(int elem_bytes, const void* src, void* dst, int N, int K, int slab,

@@ -181,3 +181,52 @@ def test_mxfp4_wide_mlp_four_column_blocks(packed):
         assert np.allclose(V, np.asarray(Vr)[:, :n_past + L], atol=4e-2, rtol=2.0 ** -7)
         sess.close()
     b.model.close()
+
+
+@pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 64, 65, 127, 128, 129, 272])
+def test_mxfp4_rows_at_the_edges_of_the_projection_tiles(rows):
+    """Every edge of the row tiles (16, 32 and 64 rows of the streaming kernel, 128 of the tile
+    kernel), with an odd number of K-steps (F = 384: 3 of 128), matrices narrower than a
+    workgroup's columns, and heads of 64 dims: logits and cells against the oracle."""
+    import torch
+    import paper_2606_29565_amd as spp
+    shape = synth.Shape("fp4edge", 2, 256, 4, 2, 64, 384, 2048, 1e4, "bf16", wfmt="mxfp4")
+    seed = 77
+    b = build_model(shape, seed, max_tokens=rows)
+    toks = synth.cpu_tokens(20 + rows, seed, 0, shape.vocab).tolist()
+    sess = spp.Session(b.model, 20 + rows + 8)
+    for i in range(0, 20, rows):
+        sess.append_delta(toks[i:min(i + rows, 20)])
+    dist = torch.empty(shape.vocab, dtype=torch.float32, device="cuda")
+    sess.preposition(toks[20:], dist)
+    torch.cuda.synchronize()
+    kvs = []
+    ref = oracle_logits(shape, seed, 20, toks[20:], prefill=toks[:20], kv_out=kvs)
+    err = max_abs(dist.cpu().numpy(), ref)
+    log(f"mxfp4 edges, {rows} rows: max|dlogit| {err:.2e}")
+    assert err <= TOL
+    for l in range(shape.n_layers):
+        K, V = read_kv(b, sess, l, 20 + rows)
+        Ko, Vo = kvs[0].layer(l)
+        # one bf16 rounding of the cell apart, and the slack of the other cell comparisons
+        for got, want in ((K, Ko[:, :20 + rows]), (V, Vo[:, :20 + rows])):
+            assert np.all(np.abs(got - want) <= 2.0 ** -7 * np.maximum(np.abs(got), np.abs(want)) + 8e-3)
+
+
+@pytest.mark.parametrize("rows", [4, 70])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_mxfp4_activations_that_are_not_finite_are_never_served(rows, bad):
+    """An embedding with an infinity or a NaN: the six-bit parts hold neither, so their block
+    scales carry it, and the distribution is flagged as it is with bf16 weights."""
+    import torch
+    import paper_2606_29565_amd as spp
+    b = build_model(SMALL, 5, max_tokens=128)
+    toks = synth.cpu_tokens(rows, 5, 0, SMALL.vocab).tolist()
+    b.weights["embed"].view(SMALL.vocab, SMALL.d_model)[toks[-1], 37] = bad
+    sess = spp.Session(b.model, rows + 8)
+    dist = torch.empty(SMALL.vocab, dtype=torch.float32, device="cuda")
+    r = sess.preposition(toks, dist)
+    torch.cuda.synchronize()
+    assert not torch.isfinite(dist).any()
+    bitmap = torch.full(((SMALL.vocab + 31) // 32,), -1, dtype=torch.int32, device="cuda")
+    assert spp.gate(r, 0.0, bitmap)[0] == spp.SPP_FALL_NONFINITE
