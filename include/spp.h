@@ -404,8 +404,9 @@ spp_status spp_gate_batch(int32_t n, const spp_ready_t* ready, const float* taus
  * call (SPP_E_INVALID_ARG beyond, nothing run), all of models on the current device.
  * Outcomes and tokens as spp_gate_batch.  Every call on a device shares that device's
  * array: the library serializes such calls per device (a call waits for the previous
- * one's results), so overlapping calls do not race; nothing in the array has to start
- * cleared, since each call writes every partial and result it reads. */
+ * one's results), so overlapping calls do not race; every partial and result a call reads
+ * is written by it, and the array's arrival counters are zero between calls (each call's
+ * last workgroup clears them). */
 spp_status spp_gate_batch_noalloc(int32_t n, const spp_ready_t* ready, const float* taus,
                                   const uint32_t* const* bitmaps, void* stream,
                                   int32_t* tokens_out, spp_gate_outcome* outcomes);

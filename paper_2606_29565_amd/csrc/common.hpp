@@ -170,45 +170,29 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
-// (value, index) pair order used by every top-2: larger value first, then lower index;
-// NaN is never a candidate (callers skip it and raise the nonfinite flag instead).
+// Top-2 of a distribution: the largest value with its lowest index, and the second largest
+// value (equal to the first where that occurs twice).  NaN is never a candidate (the callers
+// raise the nonfinite flag instead).
 struct Top2 {
   float v1, v2;
-  int i1, i2;
+  int i1;
 };
-__device__ __forceinline__ bool before(float va, int ia, float vb, int ib) {
-  return va > vb || (va == vb && ia < ib);
-}
 __device__ __forceinline__ void top2_init(Top2& t) {
   t.v1 = t.v2 = -INFINITY;
-  t.i1 = t.i2 = 0x7FFFFFFF;
+  t.i1 = 0x7FFFFFFF;
 }
+// Value v of index i, above every index pushed before (so an equal value displaces nothing).
 __device__ __forceinline__ void top2_push(Top2& t, float v, int i) {
-  if (before(v, i, t.v1, t.i1)) {
-    t.v2 = t.v1;
-    t.i2 = t.i1;
-    t.v1 = v;
-    t.i1 = i;
-  } else if (before(v, i, t.v2, t.i2)) {
-    t.v2 = v;
-    t.i2 = i;
-  }
+  t.i1 = v > t.v1 || (v == v && t.i1 == 0x7FFFFFFF) ? i : t.i1;
+  v = fmaxf(v, -INFINITY);  // NaN -> -inf
+  t.v2 = fmaxf(fminf(v, t.v1), t.v2);
+  t.v1 = fmaxf(t.v1, v);
 }
 __device__ __forceinline__ void top2_merge(Top2& t, const Top2& o) {
-  top2_push(t, o.v1, o.i1);
-  top2_push(t, o.v2, o.i2);
-}
-__device__ __forceinline__ Top2 wave_top2(Top2 t) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    Top2 u;
-    u.v1 = __shfl_xor(t.v1, o, 64);
-    u.i1 = __shfl_xor(t.i1, o, 64);
-    u.v2 = __shfl_xor(t.v2, o, 64);
-    u.i2 = __shfl_xor(t.i2, o, 64);
-    top2_merge(t, u);
-  }
-  return t;
+  const bool ob = o.v1 > t.v1 || (o.v1 == t.v1 && o.i1 < t.i1);
+  t.v2 = ob ? fmaxf(t.v1, o.v2) : fmaxf(t.v2, o.v1);
+  t.v1 = ob ? o.v1 : t.v1;
+  t.i1 = ob ? o.i1 : t.i1;
 }
 
 // ---- activations of MXFP4 projections ("a6") -------------------------------------------

@@ -140,7 +140,7 @@ struct WeightCat {
 
 // Result of a reduction over one distribution (32 bytes).
 struct ScanResult {
-  int32_t argmax, second;
+  int32_t argmax, second;  // (second: not set by the kernels)
   float top1, top2, lse;
   uint32_t flags;    // bit 0 nonfinite, bit 1 argmax in the bitmap, bit 2 the fp16
                      // attention saw an input beyond its range (see kRangeFlag)
@@ -153,10 +153,10 @@ static_assert(sizeof(ScanResult) == 32, "results are stored as two 16-byte halve
 // Per-workgroup partial of a scan.
 struct ScanPartial {
   float v1, v2;
-  int32_t i1, i2;
-  float m, s;        // running max and sum of exp(x - m) over finite values
+  int32_t i1;
   uint32_t nonfinite;
-  uint32_t pad;
+  float m, s;        // running max and sum of exp(x - m) over finite values
+  uint32_t pad[2];
 };
 
 // Kernel classes (for per-class device timing).
@@ -291,7 +291,14 @@ hipError_t final_norm_rows(const Shape& s, const StepView& v, int n_segs, const 
 // Scan of n distributions: top-2, optional log-sum-exp, bitmap bit of the argmax.  With
 // `src`: dist[b][v] = sum_split src[split][b][v] + bias[v] is formed first.
 constexpr int kScanMax = 64;        // distributions per scan launch
-constexpr int kScanMaxBlocks = 64;  // first-phase blocks per distribution
+constexpr int kScanMaxBlocks = 64;  // blocks per distribution
+// A buffer of scan partials: the partials, the arrival counters (one per distribution and one
+// for the batch; zero between launches: the last arrival clears its counter) and the results
+// of a batch before its last workgroup writes them out.  Counters start at zero when the
+// buffer is made.
+constexpr int kScanParts = kScanMax * kScanMaxBlocks;  // partials (at least lmhead_blocks)
+constexpr int kScanCounters = 16, kScanResults = kScanMax;  // in units of a partial (32 bytes)
+constexpr size_t kScanBufBytes = (size_t)(kScanParts + kScanCounters + kScanResults) * sizeof(ScanPartial);
 struct ScanJob {
   float* dist[kScanMax];
   const uint32_t* bitmap[kScanMax];  // entries may be null (empty set)
@@ -299,7 +306,7 @@ struct ScanJob {
   const float* src;            // optional [src_splits][n][V] partial logits: summed,
   int src_splits;              //   plus the bias, then written to dist[b]
   const float* bias;           // optional [V]
-  ScanPartial* parts;          // [n][scan_blocks(V, n)]
+  ScanPartial* parts;          // a buffer of kScanBufBytes
   const uint32_t* flag_src[kScanMax];  // optional words: their bit 2 is ORed into the flags
   uint32_t* done;              // optional: receives seq once every result is visible
   uint32_t seq;

@@ -110,8 +110,8 @@ struct Model {
   float2* rope = nullptr;
   void* z = nullptr;
   float* logits_rows = nullptr;
-  ScanPartial* lm_parts = nullptr;   // lmhead: lmhead_blocks; batched: [64][scan_blocks]
-  ScanPartial* gate_parts = nullptr; // [64][scan_blocks]
+  ScanPartial* lm_parts = nullptr;   // buffers of k::kScanBufBytes
+  ScanPartial* gate_parts = nullptr;
   ScanResult* gate_host = nullptr;   // pinned, device-mapped [64] results, then the done word
   ScanResult* gate_dev = nullptr;
   uint32_t gate_seq = 0;
@@ -729,7 +729,6 @@ spp_status spp_model_create(const spp_model_config* cfg, const spp_weights* w, s
   int lm_splits = 1;
   for (int n = 2; n <= c.max_sessions; ++n)
     lm_splits = std::max(lm_splits, k::gemm_plan(s, n, s.vocab, s.d).splits);
-  const int sb = k::kScanMaxBlocks;
   bool ok = true;
   auto dmal = [&](void** p, size_t b) {
     if (ok && hipMalloc(p, b) != hipSuccess) ok = false;
@@ -796,9 +795,14 @@ spp_status spp_model_create(const spp_model_config* cfg, const spp_weights* w, s
       }
     }
   }
-  const size_t lm_parts = std::max((size_t)k::lmhead_blocks(s), (size_t)k::kScanMax * sb);
-  dmal((void**)&m->lm_parts, lm_parts * sizeof(ScanPartial));
-  dmal((void**)&m->gate_parts, (size_t)k::kScanMax * sb * sizeof(ScanPartial));
+  dmal((void**)&m->lm_parts, k::kScanBufBytes);
+  dmal((void**)&m->gate_parts, k::kScanBufBytes);
+  {
+    const ScanPartial zeros[k::kScanCounters] = {};  // the arrival counters
+    for (ScanPartial* p : {m->lm_parts, m->gate_parts})
+      if (ok && hipMemcpy(p + k::kScanParts, zeros, sizeof(zeros), hipMemcpyHostToDevice) != hipSuccess)
+        ok = false;
+  }
   if (ok && hipHostMalloc((void**)&m->gate_host, (k::kScanMax + 1) * sizeof(ScanResult),
                           hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
     ok = false;
@@ -1178,9 +1182,8 @@ spp_status gate_batch_impl(int32_t n, const spp_ready_t* ready, const float* tau
         if (rc == SPP_OK) rc = wait_done(m, seq, st);
         for (int j = 0; j < ns && rc == SPP_OK; ++j) res[j] = *const_cast<const ScanResult*>(m.gate_host + j);
       } else {
-        // [kScanMax results][kScanMax * kScanMaxBlocks partials]; the partials of every
-        // used block and the results read back are written by the scan itself, so
-        // nothing has to start cleared
+        // [kScanMax results][a scan buffer]; the results read back and every partial used
+        // are written by the scan itself, and its counters are left at zero
         ScanResult* rdev = reinterpret_cast<ScanResult*>(scratch);
         for (int j = 0; j < ns; ++j) job.result[j] = rdev + j;
         job.parts = reinterpret_cast<ScanPartial*>(scratch + k::kScanMax * sizeof(ScanResult));
@@ -1206,8 +1209,7 @@ spp_status gate_batch_impl(int32_t n, const spp_ready_t* ready, const float* tau
 // scan of at most kScanMax distributions.  Each device holds its own copy of this array
 // for the life of the process; host code takes its address per device through
 // hipGetSymbolAddress (the name itself is a host-side stand-in, not a device address).
-constexpr size_t kNoallocScratchBytes =
-    k::kScanMax * sizeof(ScanResult) + (size_t)k::kScanMax * k::kScanMaxBlocks * sizeof(ScanPartial);
+constexpr size_t kNoallocScratchBytes = k::kScanMax * sizeof(ScanResult) + k::kScanBufBytes;
 static __device__ __align__(256) char scratch[kNoallocScratchBytes];
 
 namespace {

@@ -7,12 +7,12 @@
 // are dealt to the waves of the whole grid in turn, so that together they read one
 // compact window of W_lm), a butterfly shuffle sums each row, and the same wave keeps
 // a running top-2 (value desc, index asc), a running (max, sum of exp) for the
-// log-sum-exp and a nonfinite flag.  A second kernel merges the workgroup partials in
-// a fixed tree order, so the result is deterministic (no per-workgroup fences).
+// log-sum-exp and a nonfinite flag.  The last workgroup merges the partials of all in a
+// fixed tree order, so the result is deterministic.
 //
 // scan: the same reductions over already computed fp32 distributions (the gate's
-// vocabulary scan, and the batched LM head's), one grid column per distribution, then
-// one merge workgroup for the whole batch.
+// vocabulary scan, and the batched LM head's), one grid column per distribution, merged
+// by the last workgroup of each.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -39,115 +39,123 @@ __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2
   m = M;
 }
 
-__device__ __forceinline__ void acc_push(Acc& a, float v, int i, bool with_lse) {
-  if (isnan(v)) {
-    a.nonfinite = 1;
-    return;
-  }
-  if (isinf(v)) a.nonfinite = 1;
+template <bool LSE>
+__device__ __forceinline__ void acc_push(Acc& a, float v, int i) {
+  a.nonfinite |= !(fabsf(v) < INFINITY);
   top2_push(a.t, v, i);
-  if (with_lse && !isinf(v)) {
-    if (v > a.m) {
-      a.s = a.s * __expf(a.m - v) + 1.f;
-      a.m = v;
-    } else {
-      a.s += __expf(v - a.m);
+  if constexpr (LSE) {
+    if (fabsf(v) < INFINITY) {
+      if (v > a.m) {
+        a.s = a.s * __expf(a.m - v) + 1.f;
+        a.m = v;
+      } else {
+        a.s += __expf(v - a.m);
+      }
     }
   }
 }
 
+template <bool LSE>
 __device__ __forceinline__ void acc_merge(Acc& a, const Acc& b) {
   top2_merge(a.t, b.t);
-  lse_merge(a.m, a.s, b.m, b.s);
+  if constexpr (LSE) lse_merge(a.m, a.s, b.m, b.s);
   a.nonfinite |= b.nonfinite;
 }
 
-__device__ __forceinline__ Acc shfl_acc(const Acc& a, int o) {
-  Acc b;
-  b.t.v1 = __shfl_xor(a.t.v1, o, 64);
-  b.t.v2 = __shfl_xor(a.t.v2, o, 64);
-  b.t.i1 = __shfl_xor(a.t.i1, o, 64);
-  b.t.i2 = __shfl_xor(a.t.i2, o, 64);
-  b.m = __shfl_xor(a.m, o, 64);
-  b.s = __shfl_xor(a.s, o, 64);
-  b.nonfinite = __shfl_xor(a.nonfinite, o, 64);
-  return b;
-}
-
+// All 64 lanes' accumulators merged, in every lane.
+template <bool LSE>
 __device__ __forceinline__ Acc wave_acc(Acc a) {
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) acc_merge(a, shfl_acc(a, o));
+  for (int o = 1; o < 64; o <<= 1) {
+    Acc b = a;
+    b.t.v1 = __shfl_xor(a.t.v1, o, 64);
+    b.t.v2 = __shfl_xor(a.t.v2, o, 64);
+    b.t.i1 = __shfl_xor(a.t.i1, o, 64);
+    if constexpr (LSE) {
+      b.m = __shfl_xor(a.m, o, 64);
+      b.s = __shfl_xor(a.s, o, 64);
+    }
+    acc_merge<LSE>(a, b);
+  }
+  a.nonfinite = __builtin_amdgcn_ballot_w64(a.nonfinite != 0) ? 1u : 0u;
   return a;
 }
 
 __device__ __forceinline__ ScanPartial to_partial(const Acc& a) {
-  ScanPartial p;
-  p.v1 = a.t.v1;
-  p.v2 = a.t.v2;
-  p.i1 = a.t.i1;
-  p.i2 = a.t.i2;
-  p.m = a.m;
-  p.s = a.s;
-  p.nonfinite = a.nonfinite;
-  p.pad = 0;
-  return p;
+  return ScanPartial{a.t.v1, a.t.v2, a.t.i1, a.nonfinite, a.m, a.s, {0, 0}};
 }
 
 __device__ __forceinline__ Acc from_partial(const ScanPartial& p) {
-  Acc a;
-  a.t.v1 = p.v1;
-  a.t.v2 = p.v2;
-  a.t.i1 = p.i1;
-  a.t.i2 = p.i2;
-  a.m = p.m;
-  a.s = p.s;
-  a.nonfinite = p.nonfinite;
-  return a;
+  return Acc{Top2{p.v1, p.v2, p.i1}, p.m, p.s, p.nonfinite};
 }
 
-// Block-level: merge the NW waves' accumulators (wave order), result valid in thread 0.
-template <int NW = 4>
+// Block-level: merge the 4 waves' accumulators (wave order), the result in every thread.
+template <bool LSE>
 __device__ __forceinline__ Acc block_acc(Acc a, ScanPartial* red) {
-  a = wave_acc(a);
+  a = wave_acc<LSE>(a);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   __syncthreads();
   if (lane == 0) red[wave] = to_partial(a);
   __syncthreads();
   Acc r = from_partial(red[0]);
-  for (int w = 1; w < NW; ++w) acc_merge(r, from_partial(red[w]));
+  for (int w = 1; w < 4; ++w) acc_merge<LSE>(r, from_partial(red[w]));
   return r;
 }
 
-// Merges the `nb` partials of one distribution in a fixed order (so the result does not
-// depend on which workgroup finished when) and writes the result to device memory (the
-// session's summary, read after the step's completion).  Every thread of the block
-// calls it.
-__device__ void publish(const ScanPartial* parts, int nb, ScanResult* result,
-                        const uint32_t* bitmap, bool with_lse, uint32_t seq, ScanPartial* red,
-                        const uint32_t* range) {
-  Acc a;
-  acc_init(a);
-  for (int b = threadIdx.x; b < nb; b += 256) {
-    const ScanPartial p = parts[b];
-    acc_merge(a, from_partial(p));
-  }
-  a = block_acc(a, red);
-  if (threadIdx.x == 0) {
-    ScanResult r;
-    r.argmax = a.t.i1;
-    r.second = a.t.i2;
-    r.top1 = a.t.v1;
-    r.top2 = a.t.v2;
-    r.lse = (with_lse && !a.nonfinite) ? a.m + __logf(a.s) : __builtin_nanf("");
-    uint32_t flags = a.nonfinite ? 1u : 0u;
-    if (bitmap && a.t.i1 >= 0 && a.t.i1 != 0x7FFFFFFF)
-      flags |= ((bitmap[a.t.i1 >> 5] >> (a.t.i1 & 31)) & 1u) << 1;
-    if (range) flags |= *range & kRangeFlag;
-    r.flags = flags;
-    r.seq = seq;
-    r.pad = 0;
-    *result = r;
-  }
+// ---- the last workgroup of a launch merges: records handed over between workgroups
+//
+// The workgroups of a distribution sit on different XCDs, whose L2s are not coherent within a
+// kernel.  A record is stored and read with device-scope atomic accesses, which go past the
+// L2s; the store's completion is waited for before the arrival is counted, so whoever sees the
+// full count reads complete records.  A device-scope fence per workgroup would order the same
+// but writes the whole L2 back (it cost more than the second launch that this replaces).
+template <typename R>
+__device__ __forceinline__ void put_record(R* dst, const R& v) {
+  static_assert(sizeof(R) == 32 && alignof(R) <= 8, "four 8-byte stores");
+  unsigned long long w[4];
+  __builtin_memcpy(w, &v, 32);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(dst) + i, w[i], __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename R>
+__device__ __forceinline__ R get_record(const R* src) {
+  unsigned long long w[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    w[i] = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(src) + i, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+  R v;
+  __builtin_memcpy(&v, w, 32);
+  return v;
+}
+// Counts one arrival after this thread's stores have completed; true for the last of `total`,
+// which leaves the counter at zero for the next launch.
+__device__ __forceinline__ bool last_arrival(uint32_t* counter, uint32_t total) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // (compiler order)
+  __builtin_amdgcn_s_waitcnt(0);
+  const bool last = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == total - 1;
+  if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  return last;
+}
+__device__ __forceinline__ uint32_t* scan_counters(ScanPartial* parts) {
+  return reinterpret_cast<uint32_t*>(parts + k::kScanParts);
+}
+__device__ __forceinline__ ScanResult* scan_results(ScanPartial* parts) {
+  return reinterpret_cast<ScanResult*>(parts + k::kScanParts + k::kScanCounters);
+}
+
+template <bool LSE>
+__device__ __forceinline__ ScanResult make_result(const Acc& a, const uint32_t* bitmap, uint32_t range,
+                                                  uint32_t seq) {
+  uint32_t flags = a.nonfinite ? 1u : 0u;
+  if (bitmap && a.t.i1 >= 0 && a.t.i1 != 0x7FFFFFFF)
+    flags |= ((bitmap[a.t.i1 >> 5] >> (a.t.i1 & 31)) & 1u) << 1;
+  flags |= range & kRangeFlag;
+  const float lse = LSE && !a.nonfinite ? a.m + __logf(a.s) : __builtin_nanf("");
+  return ScanResult{a.t.i1, -1, a.t.v1, a.t.v2, lse, flags, seq, 0};
 }
 
 // FULL: d is a multiple of 64 * E, so every lane's chunks are in the row and the loads
@@ -160,8 +168,9 @@ __global__ __launch_bounds__(256) void lmhead_kernel(Shape s, const float* __res
                                                      float* __restrict__ dist,
                                                      const uint32_t* __restrict__ bitmap,
                                                      ScanPartial* parts,
-                                                     ScanResult* result) {
+                                                     ScanResult* result, const uint32_t* range) {
   __shared__ ScanPartial red[4];
+  __shared__ int last;
   constexpr int E = Elem<T>::kPerFrag;
   const int d = s.d, V = s.vocab;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -229,11 +238,11 @@ __global__ __launch_bounds__(256) void lmhead_kernel(Shape s, const float* __res
     db = wave_sum(db);
     const float la = da + (bias ? sa : 0.f);
     if (lane == 0) dist[r] = la;
-    acc_push(acc, la, r, true);
+    acc_push<true>(acc, la, r);
     if (r2 < V) {
       const float lb = db + (bias ? sb : 0.f);
       if (lane == 0) dist[r2] = lb;
-      acc_push(acc, lb, r2, true);
+      acc_push<true>(acc, lb, r2);
     }
   };
   // trips of this wave: rows gw + 2 nw k, k < trips
@@ -261,52 +270,91 @@ __global__ __launch_bounds__(256) void lmhead_kernel(Shape s, const float* __res
   __syncthreads();
   if (tid == 0) {
     Acc a = from_partial(red[0]);
-    for (int w = 1; w < 4; ++w) acc_merge(a, from_partial(red[w]));
-    parts[blockIdx.x] = to_partial(a);
+    for (int w = 1; w < 4; ++w) acc_merge<true>(a, from_partial(red[w]));
+    put_record(parts + blockIdx.x, to_partial(a));
+    last = last_arrival(scan_counters(parts), gridDim.x);
   }
+  __syncthreads();
+  if (!last) return;
+  // the last workgroup merges the partials in a fixed order (so the result does not depend on
+  // which one it is) and writes the session's summary
+  acc_init(acc);
+  for (int b = tid; b < (int)gridDim.x; b += 256) acc_merge<true>(acc, from_partial(get_record(parts + b)));
+  acc = block_acc<true>(acc, red);
+  if (tid == 0) *result = make_result<true>(acc, bitmap, range ? *range : 0u, 1u);
 }
 
-// The LM head's second phase: merges the workgroups' partials in order and publishes.
-__global__ __launch_bounds__(256) void lmhead_merge_kernel(const ScanPartial* parts, int nb,
-                                                           ScanResult* result,
-                                                           const uint32_t* bitmap,
-                                                           const uint32_t* range) {
+// What one distribution of a scan needs, from the batch's job or from a job of one (whose
+// argument block is 25 times smaller: the workgroups read it from host memory).
+struct ScanJob1 {
+  float* dist1;
+  const uint32_t* bitmap1;
+  ScanResult* result1;
+  const uint32_t* flag_src1;
+  ScanPartial* parts;
+  uint32_t* done;
+  uint32_t seq;
+  __device__ float* dist_of(int) const { return dist1; }
+  __device__ const uint32_t* bitmap_of(int) const { return bitmap1; }
+  __device__ ScanResult* result_of(int) const { return result1; }
+  __device__ const uint32_t* flags_of(int) const { return flag_src1; }
+  __device__ const float* src_of(int, int) const { return nullptr; }
+  __device__ float4 load4(const float* dist, const float*, int64_t, int v) const {
+    return *reinterpret_cast<const float4*>(dist + v);
+  }
+  __device__ float load1(const float* dist, const float*, int64_t, int v) const { return dist[v]; }
+};
+struct ScanJobN {
+  k::ScanJob j;
+  ScanPartial* parts;
+  uint32_t* done;
+  uint32_t seq;
+  __device__ float* dist_of(int b) const { return j.dist[b]; }
+  __device__ const uint32_t* bitmap_of(int b) const { return j.bitmap[b]; }
+  __device__ ScanResult* result_of(int b) const { return j.result[b]; }
+  __device__ const uint32_t* flags_of(int b) const { return j.flag_src[b]; }
+  // With `src`, dist[b][v] = sum over splits of src[split][b][v] (+ bias[v]) is formed and
+  // stored on the way.
+  __device__ const float* src_of(int b, int V) const { return j.src ? j.src + (int64_t)b * V : nullptr; }
+  __device__ float4 load4(const float* dist, const float* src, int64_t sstride, int v) const {
+    if (!src) return *reinterpret_cast<const float4*>(dist + v);
+    float4 q = *reinterpret_cast<const float4*>(src + v);
+    for (int k = 1; k < j.src_splits; ++k) {
+      const float4 p = *reinterpret_cast<const float4*>(src + k * sstride + v);
+      q = make_float4(q.x + p.x, q.y + p.y, q.z + p.z, q.w + p.w);
+    }
+    if (j.bias) {
+      const float4 bb = *reinterpret_cast<const float4*>(j.bias + v);
+      q = make_float4(q.x + bb.x, q.y + bb.y, q.z + bb.z, q.w + bb.w);
+    }
+    return q;
+  }
+  __device__ float load1(const float* dist, const float* src, int64_t sstride, int v) const {
+    if (!src) return dist[v];
+    float y = src[v];
+    for (int k = 1; k < j.src_splits; ++k) y += src[k * sstride + v];
+    return j.bias ? y + j.bias[v] : y;
+  }
+};
+
+// One launch: grid (blocks, distributions).  Block x of distribution b takes an equal share of
+// the vocabulary's 16-byte units (the last block also takes the scalar tail when vocab % 4 != 0),
+// all its loads in flight at once.  The last workgroup of a distribution merges its partials
+// (lane l partial l, nb <= 64) in a fixed order, and the last of the batch writes all results
+// (lane b result b).  When they go to host memory (job.done), that one wave makes them visible
+// to the host (one system-scope fence, which writes back its L2) and publishes the batch's
+// sequence number: a fence per distribution, or per wave, would write the L2 back that many
+// times.  With the merge as a second launch and branches in the push, a gate call through the
+// Python binding took 28.0 us for one distribution of 128256 and 45.4 us for 64; now 22.6 and
+// 36.4 (same box).
+template <typename J, bool LSE>
+__global__ __launch_bounds__(256) void scan_kernel(int V, J job) {
+  constexpr int TPB = 256;
   __shared__ ScanPartial red[4];
-  publish(parts, nb, result, bitmap, true, 1u, red, range);
-}
-
-// First phase of a scan: grid (blocks, distributions).  Block x of distribution b takes
-// an equal share of the vocabulary's 16-byte units (the last block also takes the scalar
-// tail when vocab % 4 != 0) and keeps four of its loads in flight per thread.  With
-// `src`, dist[b][v] = sum over splits of src[split][b][v] (+ bias[v]) is formed and
-// stored on the way.
-__device__ __forceinline__ float4 scan_load4(const k::ScanJob& job, const float* dist, const float* src,
-                                             int64_t sstride, int v) {
-  if (!src) return *reinterpret_cast<const float4*>(dist + v);
-  float4 q = *reinterpret_cast<const float4*>(src + v);
-  for (int k = 1; k < job.src_splits; ++k) {
-    const float4 p = *reinterpret_cast<const float4*>(src + k * sstride + v);
-    q.x += p.x;
-    q.y += p.y;
-    q.z += p.z;
-    q.w += p.w;
-  }
-  if (job.bias) {
-    const float4 bb = *reinterpret_cast<const float4*>(job.bias + v);
-    q.x += bb.x;
-    q.y += bb.y;
-    q.z += bb.z;
-    q.w += bb.w;
-  }
-  return q;
-}
-
-template <int TPB>
-__global__ __launch_bounds__(TPB) void scan_kernel(int V, k::ScanJob job) {
-  __shared__ ScanPartial red[TPB / 64];
-  const int b = blockIdx.y, nb = gridDim.x, n = gridDim.y;
-  float* dist = job.dist[b];
-  const float* src = job.src ? job.src + (int64_t)b * V : nullptr;
+  __shared__ int last;
+  const int b = blockIdx.y, nb = gridDim.x, n = gridDim.y, tid = threadIdx.x;
+  float* dist = job.dist_of(b);
+  const float* src = job.src_of(b, V);
   const int64_t sstride = (int64_t)n * V;  // between partial splits of src
   Acc a;
   acc_init(a);
@@ -315,98 +363,68 @@ __global__ __launch_bounds__(TPB) void scan_kernel(int V, k::ScanJob job) {
     const int u0 = (int)((int64_t)blockIdx.x * V4 / nb), u1 = (int)((int64_t)(blockIdx.x + 1) * V4 / nb);
     constexpr int IN = 8;  // loads in flight per thread: one round trip per block
                            // (scan_launch gives a block at most ~8 units per thread)
-    for (int u = u0 + threadIdx.x; u < u1; u += IN * TPB) {
+    for (int u = u0 + tid; u < u1; u += IN * TPB) {
       float4 q[IN];
 #pragma unroll
       for (int i = 0; i < IN; ++i) {
         const int ui = u + i * TPB;
-        if (ui < u1) q[i] = scan_load4(job, dist, src, sstride, 4 * ui);
+        if (ui < u1) q[i] = job.load4(dist, src, sstride, 4 * ui);
       }
 #pragma unroll
       for (int i = 0; i < IN; ++i) {
         const int ui = u + i * TPB;
         if (ui < u1) {
           if (src) *reinterpret_cast<float4*>(dist + 4 * ui) = q[i];
-          acc_push(a, q[i].x, 4 * ui, job.with_lse);
-          acc_push(a, q[i].y, 4 * ui + 1, job.with_lse);
-          acc_push(a, q[i].z, 4 * ui + 2, job.with_lse);
-          acc_push(a, q[i].w, 4 * ui + 3, job.with_lse);
+          acc_push<LSE>(a, q[i].x, 4 * ui);
+          acc_push<LSE>(a, q[i].y, 4 * ui + 1);
+          acc_push<LSE>(a, q[i].z, 4 * ui + 2);
+          acc_push<LSE>(a, q[i].w, 4 * ui + 3);
         }
       }
     }
   } else {
     const int v0 = (int)((int64_t)blockIdx.x * V / nb), v1 = (int)((int64_t)(blockIdx.x + 1) * V / nb);
-    for (int v = v0 + threadIdx.x; v < v1; v += TPB) {
-      float y;
-      if (src) {
-        y = src[v];
-        for (int k = 1; k < job.src_splits; ++k) y += src[k * sstride + v];
-        if (job.bias) y += job.bias[v];
-        dist[v] = y;
-      } else {
-        y = dist[v];
-      }
-      acc_push(a, y, v, job.with_lse);
+    for (int v = v0 + tid; v < v1; v += TPB) {
+      const float y = job.load1(dist, src, sstride, v);
+      if (src) dist[v] = y;
+      acc_push<LSE>(a, y, v);
     }
   }
-  a = block_acc<TPB / 64>(a, red);
-  if (threadIdx.x == 0) job.parts[(int64_t)b * nb + blockIdx.x] = to_partial(a);
-}
-
-// Second phase of the scan: ONE workgroup of 16 waves merges every distribution's
-// partials (wave w takes distributions w, w + 16, ...; lane l holds partial l, nb <= 64)
-// in a fixed order into LDS; then wave 0 writes all results (lane b result b).  When the
-// results go to host memory (job.done), that one wave makes them visible to the host
-// (one system-scope fence, which writes back its L2) and publishes the batch's sequence
-// number: a fence per distribution, or per wave, would write the L2 back that many times.
-__global__ __launch_bounds__(1024) void scan_merge_kernel(int n, int nb, k::ScanJob job) {
-  __shared__ __attribute__((aligned(32))) ScanResult res[k::kScanMax];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  // every partial this lane merges is requested before the first is used: one round trip
-  constexpr int PER = k::kScanMax / 16;  // distributions per wave
-  ScanPartial pp[PER];
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int b = wave + 16 * q;
-    if (b < n && lane < nb) pp[q] = job.parts[(int64_t)b * nb + lane];
-  }
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int b = wave + 16 * q;
-    if (b >= n) break;
-    Acc a;
-    acc_init(a);
-    if (lane < nb) a = from_partial(pp[q]);
-    a = wave_acc(a);
-    if (lane == 0) {
-      ScanResult r;
-      r.argmax = a.t.i1;
-      r.second = a.t.i2;
-      r.top1 = a.t.v1;
-      r.top2 = a.t.v2;
-      r.lse = (job.with_lse && !a.nonfinite) ? a.m + __logf(a.s) : __builtin_nanf("");
-      uint32_t flags = a.nonfinite ? 1u : 0u;
-      const uint32_t* bitmap = job.bitmap[b];
-      if (bitmap && a.t.i1 >= 0 && a.t.i1 != 0x7FFFFFFF)
-        flags |= ((bitmap[a.t.i1 >> 5] >> (a.t.i1 & 31)) & 1u) << 1;
-      if (job.flag_src[b]) flags |= *job.flag_src[b] & kRangeFlag;
-      r.flags = flags;
-      r.seq = job.seq;
-      r.pad = 0;
-      res[b] = r;
-    }
+  a = block_acc<LSE>(a, red);
+  if (tid == 0) {
+    put_record(job.parts + (int64_t)b * nb + blockIdx.x, to_partial(a));
+    last = last_arrival(scan_counters(job.parts) + b, nb);
   }
   __syncthreads();
-  if (wave != 0) return;
-  if (lane < n) {  // two 16-byte stores per result (the record is 32-byte aligned)
-    const uint4* src = reinterpret_cast<const uint4*>(&res[lane]);
-    uint4* dst = reinterpret_cast<uint4*>(job.result[lane]);
-    dst[0] = src[0];
-    dst[1] = src[1];
+  if (!last || tid >= 64) return;
+  // the distribution's last workgroup, one wave
+  acc_init(a);
+  const uint32_t* fs = job.flags_of(b);
+  const uint32_t range = fs ? *fs : 0u;
+  if (tid < nb) a = from_partial(get_record(job.parts + (int64_t)b * nb + tid));
+  a = wave_acc<LSE>(a);
+  ScanResult r{};
+  bool final = true;
+  if (tid == 0) {
+    r = make_result<LSE>(a, job.bitmap_of(b), range, job.seq);
+    if (n > 1) {
+      put_record(scan_results(job.parts) + b, r);
+      final = last_arrival(scan_counters(job.parts) + k::kScanMax, n);
+    }
+  }
+  if (!__shfl((int)final, 0, 64)) return;
+  // the batch's last workgroup
+  if (n > 1 && tid < n) r = get_record(scan_results(job.parts) + tid);
+  if (tid < n) {  // two 16-byte stores per result (the record is 32-byte aligned)
+    uint4 w[2];
+    __builtin_memcpy(w, &r, 32);
+    uint4* dst = reinterpret_cast<uint4*>(job.result_of(tid));
+    dst[0] = w[0];
+    dst[1] = w[1];
   }
   if (job.done) {
     __threadfence_system();  // every lane's results, before the number the host polls
-    if (lane == 0) *reinterpret_cast<volatile uint32_t*>(job.done) = job.seq;
+    if (tid == 0) *reinterpret_cast<volatile uint32_t*>(job.done) = job.seq;
     __threadfence_system();
   }
 }
@@ -425,10 +443,10 @@ hipError_t launch_lmhead(const Shape& s, const float* x_row, const void* g_final
 #define SPP_LMHEAD(NCV)                                                                        \
   if (full)                                                                                    \
     SPP_LAUNCH((lmhead_kernel<T, NCV, true>), dim3(nb), dim3(256), 0, st, s, x_row, g, W, bias, \
-               dist, bitmap, parts, result);                                                   \
+               dist, bitmap, parts, result, range);                                            \
   else                                                                                         \
     SPP_LAUNCH((lmhead_kernel<T, NCV, false>), dim3(nb), dim3(256), 0, st, s, x_row, g, W, bias, \
-               dist, bitmap, parts, result)
+               dist, bitmap, parts, result, range)
   switch (nc) {
     case 1: SPP_LMHEAD(1); break;
     case 2: SPP_LMHEAD(2); break;
@@ -439,7 +457,6 @@ hipError_t launch_lmhead(const Shape& s, const float* x_row, const void* g_final
     default: return hipErrorInvalidValue;
   }
 #undef SPP_LMHEAD
-  SPP_LAUNCH(lmhead_merge_kernel, dim3(1), dim3(256), 0, st, parts, nb, result, bitmap, range);
   return hipGetLastError();
 }
 
@@ -493,8 +510,17 @@ hipError_t scan(const Shape& s, int n, const ScanJob& job, hipStream_t st) {
   if (n > kScanMax) return hipErrorInvalidValue;
   int nb, tpb;
   scan_launch(s.vocab, n, &nb, &tpb);
-  SPP_LAUNCH(scan_kernel<256>, dim3(nb, n), dim3(tpb), 0, st, s.vocab, job);
-  SPP_LAUNCH(scan_merge_kernel, dim3(1), dim3(1024), 0, st, n, nb, job);
+  const dim3 grid(nb, n), block(tpb);
+  if (n == 1 && !job.src && !job.with_lse) {
+    const ScanJob1 j{job.dist[0], job.bitmap[0], job.result[0], job.flag_src[0], job.parts, job.done, job.seq};
+    SPP_LAUNCH((scan_kernel<ScanJob1, false>), grid, block, 0, st, s.vocab, j);
+  } else {
+    const ScanJobN j{job, job.parts, job.done, job.seq};
+    if (job.with_lse)
+      SPP_LAUNCH((scan_kernel<ScanJobN, true>), grid, block, 0, st, s.vocab, j);
+    else
+      SPP_LAUNCH((scan_kernel<ScanJobN, false>), grid, block, 0, st, s.vocab, j);
+  }
   return hipGetLastError();
 }
 

@@ -164,3 +164,44 @@ def test_gate_latency_single_distribution():
     log(f"gate e2e: p50 {ts[150]:.1f} us, p99 {ts[297]:.1f} us")
     assert ts[150] < 500.0
     sess.close()
+
+
+@pytest.mark.parametrize("V,n", [(16, 1), (16, 3), (1000, 1), (1008, 64), (4096, 2), (50000, 17),
+                                 (50001, 1), (128256, 63)])
+def test_scan_merges_of_every_launch_shape_and_their_counters(V, n):
+    """One block, several blocks and 64 of them per distribution, the scalar path (V % 4 != 0),
+    1 to 64 distributions of one launch, called again and again with other values: every call
+    finds its counters at zero, and the merge in the last workgroup gives the exact top-2 with
+    the lowest index on ties, whichever workgroup is the last."""
+    import torch
+    import paper_2606_29565_amd as spp
+    b, shape = _ready_session(V, max_sessions=1 if n == 1 else 64)
+    x = torch.empty((n, V), dtype=torch.float32, device="cuda")
+    sessions = [spp.Session(b.model, 16) for _ in range(n)]
+    readies = [s.preposition([1], x[i]) for i, s in enumerate(sessions)]
+    for r in readies:
+        spp.ready_summary(r)
+    rng = np.random.default_rng(V + n)
+    full = torch.full(((V + 31) // 32,), -1, dtype=torch.int32, device="cuda")
+    for trial in range(6):
+        # (few distinct values: ties everywhere, over block and lane borders)
+        vals = rng.integers(-3, 4, (n, V)).astype(np.float32)
+        if trial % 2:
+            vals[np.arange(n), rng.integers(0, V, n)] = 5.0
+        if trial == 4:
+            vals[:, : V // 2] = -np.inf
+        x.copy_(torch.from_numpy(vals))
+        torch.cuda.synchronize()
+        calls = [spp.gate_batch(readies, [0.5] * n, [full] * n),
+                 spp.gate_batch(readies, [0.5] * n, [full] * n, noalloc=True)]
+        for i in range(n):
+            order = np.sort(vals[i])
+            top, gap = int(np.argmax(vals[i])), order[-1] - order[-2]
+            want = spp.SPP_FALL_NONFINITE if trial == 4 else (
+                spp.SPP_SERVED if gap > 0.5 else spp.SPP_FALL_GAP)
+            for res in calls:
+                assert res[i] == (want, top if want == spp.SPP_SERVED else -1)
+            out, tok, s = spp.gate(readies[i], 0.5, full)
+            assert (out, s.argmax, s.top1, s.top2) == (want, top, order[-1], order[-2])
+    for s in sessions:
+        s.close()
