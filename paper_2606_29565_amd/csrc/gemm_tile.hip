@@ -1,0 +1,289 @@
+// Projections of bf16 models over many rows (more than 128):
+//   P[split][M][N] = X[M][K-range of split] . W[N][K-range]^T,  X = hi + lo
+// where the products, not the weight stream, bound the kernel: every weight meets two bf16
+// halves of each activation.
+//
+// A workgroup of 4 waves takes 128 rows x 256 columns; two workgroups share a CU, and while one
+// waits the other multiplies.  A wave owns 32 rows and all the columns.  Its activations belong
+// to it alone, so they go from memory straight to its registers as operands; only the weights,
+// which the four waves share, pass through LDS (the stored tiles are in operand order, so LDS
+// is written and read in whole linear kilobytes), in two buffers, with one barrier per
+// 64-element step and the step after next in flight in registers.  An operand read from LDS
+// feeds four products (two row tiles, two halves).  A step takes 1.6 us of a CU; its products
+// alone take 1.3 at the 1.63 PFLOP/s that the matrix cores sustain from registers.
+// 8B shape, same box, against 64-row tiles with the activations in LDS (2467 rows) and 128-row
+// passes over all weights (203 rows): the 64-session pass over 2 layers 5489 -> 5129 us (gate/up
+// + SwiGLU 1043 -> 935 per layer, QKV 238 -> 219, O and down within 2%), the 203-row append over
+// 4 layers 1462 -> 1198 us (gate/up + SwiGLU 150 -> 124, QKV 41 -> 34, O 32 -> 26, down 73 -> 62).
+// 128-column tiles (twice the activation traffic per product) took 1.3-1.4 times as long at 2467
+// rows, and at 128 rows and fewer the passes of gemm.hip stay ahead (166 us per layer, 178 here).
+#include <algorithm>
+
+#include "common.hpp"
+#include "kernels.hpp"
+
+namespace spp {
+namespace {
+
+constexpr int kRows = 128;        // rows of a workgroup
+constexpr int CB = 16;            // its column blocks of 16
+constexpr int kStep = 64;         // elements of a step
+constexpr int kBlock = 2048;      // bytes of a weight block: 16 rows x one step, two 1 KB operands
+
+struct SwigluTile {
+  const float* ss;
+  int nb, d;
+  float eps;
+  bf16_t* act;
+  bf16_t* act_lo;
+  int F;
+};
+
+struct TileBlock {
+  const char* base;  // the matrix
+  int cb, nblk;
+};
+__device__ __forceinline__ TileBlock tile_block(const WeightCat& w, int n) {
+  // past the last column: block 0 of the first matrix (always there), whose result is not kept
+  const int nn = n < w.nbeg[3] ? n : 0;
+  const int mi = nn >= w.nbeg[2] ? 2 : (nn >= w.nbeg[1] ? 1 : 0);
+  const void* mat = mi == 2 ? w.mat[2] : (mi == 1 ? w.mat[1] : w.mat[0]);
+  const int nb = mi == 2 ? w.nbeg[2] : (mi == 1 ? w.nbeg[1] : w.nbeg[0]);
+  const int ne = mi == 2 ? w.nbeg[3] : (mi == 1 ? w.nbeg[2] : w.nbeg[1]);
+  return TileBlock{static_cast<const char*>(mat), (nn - nb) / 16, (ne - nb) / 16};
+}
+
+// c[n][row] += W[n][k] x[row][k] over 32 elements: lane 16 g + r holds weight row r and
+// activation row r at k = 8 g + 0..7; c is weight rows 4 g .. 4 g + 3 of activation row r.
+__device__ __forceinline__ f32x4 mma(const uint4& w, const uint4& x, f32x4 c) {
+  return mma_frag(w, x, c, bf16_t{});
+}
+
+template <bool SW>
+__global__ __launch_bounds__(256, 2) void tile_kernel(const bf16_t* __restrict__ X,
+                                                      const bf16_t* __restrict__ Xlo, int M, int K,
+                                                      WeightCat w, int N, float* __restrict__ P,
+                                                      SwigluTile so, int splits, int groups,
+                                                      int row_tiles, int band) {
+  constexpr int NW = 4, PER = CB / NW, STAGE = CB * kBlock;
+  __shared__ __attribute__((aligned(16))) char lds[2][STAGE];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, r = lane & 15;
+
+  // Workgroup id goes to XCD id % 8, slot id / 8.  An XCD's consecutive slots take `band` row
+  // tiles of one (split, column group) and then the next group: the activations of a band and
+  // the weights of a group are both shared in its L2.
+  const int slot = blockIdx.x >> 3, xcd = blockIdx.x & 7;
+  const int octs = (splits * groups + 7) / 8, per_band = octs * band;
+  const int rb = slot / per_band, in = slot - rb * per_band;
+  const int xy = in / band * 8 + xcd, tile_m = rb * band + in % band;
+  if (xy >= splits * groups || tile_m >= row_tiles) return;
+  const int split = xy % splits, cgroup = xy / splits;
+  const int ksteps = K / kStep;
+  const int k0 = (int)((int64_t)split * ksteps / splits), k1 = (int)((int64_t)(split + 1) * ksteps / splits);
+  const int row0 = tile_m * kRows + wave * 32;
+
+  auto column = [&](int b) {  // first column of block b, in the concatenated matrices
+    if constexpr (SW) {       // CB / 2 blocks of the gate and the same of the up matrix
+      const int f = (cgroup * (CB / 2) + b % (CB / 2)) * 16;
+      return f < so.F ? (b < CB / 2 ? f : so.F + f) : w.nbeg[3];
+    } else {
+      return (cgroup * CB + b) * 16;
+    }
+  };
+  TileBlock blk[PER];  // the blocks this wave brings in: wave, wave + NW, ...
+#pragma unroll
+  for (int i = 0; i < PER; ++i) blk[i] = tile_block(w, column(wave + i * NW));
+
+  // Both operands are walked step by step: uniform bases that advance, and offsets that stay.
+  // Past the range the last step is loaded again and never used.
+  const int nslab = ksteps / w.slab;
+  int ts = k0 % w.slab, sl = k0 / w.slab, pos = ts * nslab + sl;  // (time-major position)
+  int wleft = k1 - k0, aleft = k1 - k0;
+  struct Weights {
+    uint4 f[PER][2];
+  };
+  auto load_w = [&](Weights& x) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const char* p = blk[i].base + ((int64_t)pos * blk[i].nblk + blk[i].cb) * kBlock + (uint32_t)lane * 16;
+      x.f[i][0] = ld_global(p);
+      x.f[i][1] = ld_global(p + 1024);
+    }
+    const bool go = wleft > 1, wrap = ts + 1 == w.slab;
+    wleft -= go ? 1 : 0;
+    sl += go && wrap ? 1 : 0;
+    pos = go ? (wrap ? sl : pos + nslab) : pos;
+    ts = go ? (wrap ? 0 : ts + 1) : ts;
+  };
+  auto store_w = [&](char* buf, const Weights& x) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      char* p = buf + (wave + i * NW) * kBlock + lane * 16;
+      *reinterpret_cast<uint4*>(p) = x.f[i][0];
+      *reinterpret_cast<uint4*>(p + 1024) = x.f[i][1];
+    }
+  };
+  struct Act {
+    uint4 x[2][2][2];  // [operand of 32 elements][row tile][hi, lo]
+  };
+  const int64_t base = (int64_t)min(row0, M - 1) * K + (int64_t)k0 * kStep;  // uniform
+  const char *ah = reinterpret_cast<const char*>(X + base), *al = reinterpret_cast<const char*>(Xlo + base);
+  uint32_t aoff[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)  // (rows past M read row M - 1)
+    aoff[t] = (uint32_t)(min(row0 + t * 16 + r, M - 1) - min(row0, M - 1)) * (uint32_t)K * 2u + g * 16;
+  auto load_half = [&](Act& a, int j) {  // operand j of a step; the second one advances
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      a.x[j][t][0] = ld_global(ah + aoff[t] + j * 64);
+      a.x[j][t][1] = ld_global(al + aoff[t] + j * 64);
+    }
+    if (j == 1) {
+      const int adv = aleft > 1 ? kStep * 2 : 0;
+      ah += adv;
+      al += adv;
+      aleft -= aleft > 1 ? 1 : 0;
+    }
+  };
+
+  f32x4 acc[2][CB];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int c = 0; c < CB; ++c) acc[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](const char* buf, const Act& a, int j) {
+    const char* wb = buf + lane * 16 + j * 1024;
+#pragma unroll
+    for (int c = 0; c < CB; c += 2) {
+      const uint4 q0 = *reinterpret_cast<const uint4*>(wb + c * kBlock);
+      const uint4 q1 = *reinterpret_cast<const uint4*>(wb + (c + 1) * kBlock);
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          acc[t][c] = mma(q0, a.x[j][t][p], acc[t][c]);
+          acc[t][c + 1] = mma(q1, a.x[j][t][p], acc[t][c + 1]);
+        }
+    }
+  };
+  // One step: the weights of the step after go from registers to the other buffer, and their
+  // registers take the next step not yet requested; an operand's registers are reloaded as soon
+  // as its products are issued, for the next step that uses them.  The barriers keep that order,
+  // which the waits rely on (a prologue in another order made every step wait for its newest
+  // loads).
+  auto step = [&](const char* buf, char* next, Act& a, Weights& x) {
+    __syncthreads();  // buf holds this step; next is free
+    store_w(next, x);
+    load_w(x);
+    __builtin_amdgcn_sched_barrier(0);
+    compute(buf, a, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_half(a, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    compute(buf, a, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    load_half(a, 1);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  Weights w0;
+  Act a0;
+  load_w(w0);
+  store_w(lds[0], w0);
+  __builtin_amdgcn_sched_barrier(0);
+  load_w(w0);
+  __builtin_amdgcn_sched_barrier(0);
+  load_half(a0, 0);
+  load_half(a0, 1);
+  __builtin_amdgcn_sched_barrier(0);
+  // (rolled: two copies of the body did not fit the registers)
+#pragma unroll 1
+  for (int ks = k0, at = 0; ks < k1; ++ks, at ^= 1) step(lds[at], lds[at ^ 1], a0, w0);
+
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int row = row0 + t * 16 + r;
+    if (row >= M) continue;
+    if constexpr (SW) {
+      const float inv = row_inv(so.ss, row, so.nb, so.d, so.eps);
+#pragma unroll
+      for (int c = 0; c < CB / 2; ++c) {
+        const int f = (cgroup * (CB / 2) + c) * 16;
+        if (f >= so.F) continue;
+        float o[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float a = acc[t][c][i] * inv;
+          o[i] = a / (1.f + __expf(-a)) * (acc[t][c + CB / 2][i] * inv);
+        }
+        store_act4(so.act, so.act_lo, (int64_t)row * so.F + f + 4 * g, make_float4(o[0], o[1], o[2], o[3]));
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < CB; ++c) {
+        const int n = (cgroup * CB + c) * 16;
+        if (n < w.nbeg[3])
+          *reinterpret_cast<f32x4*>(P + ((int64_t)split * M + row) * N + n + 4 * g) = acc[t][c];
+      }
+    }
+  }
+}
+
+template <bool SW>
+hipError_t launch(const k::GemmPlan& p, const void* X, const void* Xlo, int M, int K, const WeightCat& w,
+                  int N, float* P, const SwigluTile& so, hipStream_t st) {
+  const int groups = (N + 16 * CB - 1) / (16 * CB), band = std::min(p.row_tiles, 8);
+  const int bands = (p.row_tiles + band - 1) / band, octs = (p.splits * groups + 7) / 8;
+  SPP_LAUNCH((tile_kernel<SW>), dim3((unsigned)(bands * band * octs * 8)), dim3(256), 0, st,
+             static_cast<const bf16_t*>(X), static_cast<const bf16_t*>(Xlo), M, K, w, N, P, so, p.splits,
+             groups, p.row_tiles, band);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+namespace k {
+
+// The K-split count whose estimated time is least: a CU takes 1.6 us per workgroup and step (one
+// workgroup alone, or two in turn), and the fp32 partials are written and read at 4 TB/s.
+// (8B down projection of 2467 rows, 1 to 6 splits: 670, 532, 495, 470, 528, 512 us.)
+GemmPlan gemm_plan_tile(int M, int N, int K, bool split) {
+  GemmPlan p{};
+  const int ksteps = K / kStep, groups = (N + 16 * CB - 1) / (16 * CB);
+  p.row_tiles = (M + kRows - 1) / kRows;
+  p.splits = p.iters = 1;
+  double best = 0;
+  for (int sp = 1; split && sp <= 8 && (sp == 1 || sp * 4 <= ksteps); ++sp) {
+    const int64_t wgs = (int64_t)p.row_tiles * groups * sp;
+    const double t = (double)((wgs + 255) / 256) * ((ksteps + sp - 1) / sp) * 1.6 +
+                     (double)sp * M * N * 8.0 / 4.0e6;
+    if (sp == 1 || t < best) {
+      best = t;
+      p.splits = sp;
+    }
+  }
+  return p;
+}
+
+hipError_t gemm_tile(const GemmPlan& p, const void* X, const void* Xlo, int M, int K,
+                     const WeightCat& w, int N, float* partials, hipStream_t st) {
+  if (p.row_tiles != (M + kRows - 1) / kRows || K % kStep || p.splits < 1 || p.splits > K / kStep ||
+      w.nbeg[3] != N)
+    return hipErrorInvalidValue;
+  return launch<false>(p, X, Xlo, M, K, w, N, partials, SwigluTile{}, st);
+}
+
+hipError_t gemm_tile_swiglu(const Shape& s, const GemmPlan& p, const void* X, const void* Xlo, int M,
+                            int K, const WeightCat& w, int F, const float* ss, void* act, void* act_lo,
+                            hipStream_t st) {
+  if (p.row_tiles != (M + kRows - 1) / kRows || K % kStep || p.splits != 1 || F % 16 ||
+      w.nbeg[1] != F || w.nbeg[3] != 2 * F)
+    return hipErrorInvalidValue;
+  const SwigluTile so{ss, res_blocks(s), s.d, s.eps, static_cast<bf16_t*>(act),
+                      static_cast<bf16_t*>(act_lo), F};
+  return launch<true>(p, X, Xlo, M, K, w, 2 * F, nullptr, so, st);
+}
+
+}  // namespace k
+}  // namespace spp

@@ -216,6 +216,17 @@ hipError_t gemm_swiglu(const Shape& s, const GemmPlan& p, const void* X, const v
                        hipStream_t st);
 int pack_slab_steps_gateup(const Shape& s, int F, int K);
 
+// The same two projections of bf16 models over more than kTileRows rows (row_tiles tiles of 128
+// rows; splits of whole K-steps, not all alike): gemm_plan, gemm_plan_swiglu, gemm and
+// gemm_swiglu pass them on.  split = false: no K-splits (the fused form).
+constexpr int kTileRows = 128;
+GemmPlan gemm_plan_tile(int M, int N, int K, bool split);
+hipError_t gemm_tile(const GemmPlan& p, const void* X, const void* Xlo, int M, int K,
+                     const WeightCat& w, int N, float* partials, hipStream_t st);
+hipError_t gemm_tile_swiglu(const Shape& s, const GemmPlan& p, const void* X, const void* Xlo, int M,
+                            int K, const WeightCat& w, int F, const float* ss, void* act, void* act_lo,
+                            hipStream_t st);
+
 // Rearranges a row-major [N][K] matrix into the tiled layout the GEMM streams.  Blocks
 // of 16 rows x one 128-byte K-step (2 KB: two 1 KB fragments in lane order) are ordered
 // time-major: block (row block cb, K-step ks) goes to position

@@ -543,3 +543,31 @@ def test_stream8b_full_model_every_logit_and_gate():
                 assert tok == s.argmax
             decided += 1
     assert decided >= 3 and any(o == spp.SPP_SERVED for o, _ in outcomes.values())
+
+
+@pytest.mark.parametrize("rows", [129, 144, 160, 255, 256, 257, 400])
+def test_many_row_projection_tiles_at_their_edges(rows):
+    """The 128-row, 256-column tiles of bf16 projections: a tile of one row, a partly filled wave
+    and a full one, odd numbers of K-steps (d = 320: 5 of 64, F = 448: 7), matrices narrower
+    than a tile and several per tile (Q, K and V): logits and cells against the oracle."""
+    import torch
+    import paper_2606_29565_amd as spp
+    shape = synth.Shape("tileedge", 2, 320, 5, 1, 64, 448, 2048, 1e4, "bf16")
+    seed = 91
+    b = build_model(shape, seed, max_tokens=rows)
+    toks = synth.cpu_tokens(rows, seed, 0, shape.vocab).tolist()
+    sess = spp.Session(b.model, rows + 8)
+    dist = torch.empty(shape.vocab, dtype=torch.float32, device="cuda")
+    sess.preposition(toks, dist)
+    torch.cuda.synchronize()
+    kvs = []
+    ref = oracle_logits(shape, seed, 0, toks, kv_out=kvs)
+    err = max_abs(dist.cpu().numpy(), ref)
+    log(f"many-row tiles, {rows} rows: max|dlogit| {err:.2e}")
+    assert err <= LOGIT_TOL
+    for l in range(shape.n_layers):
+        K, V = read_kv(b, sess, l, rows)
+        Ko, Vo = kvs[0].layer(l)
+        # one bf16 rounding of the cell apart, and the slack of the other cell comparisons
+        for got, want in ((K, Ko[:, :rows]), (V, Vo[:, :rows])):
+            assert np.all(np.abs(got - want) <= 2.0 ** -7 * np.maximum(np.abs(got), np.abs(want)) + 8e-3)
