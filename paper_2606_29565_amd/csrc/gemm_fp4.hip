@@ -306,9 +306,9 @@ __global__ __launch_bounds__(64 * NW) void stream4_kernel(const char* __restrict
 // 128 costs a SIMD with two waves 2048 cycles of products and the CU 139 KB of LDS reads, 17 KB
 // of LDS writes and 68 KB from L2.  SW: 8 of a wave's 16 column blocks are of the gate and the
 // same 8 of the up matrix (F is a multiple of 128).
-// 700 rows of one 70B layer: gate/up + SwiGLU 1386 -> 685 us (960 TFLOP/s of the projection),
-// QKV 353 -> 116, O 184 -> 103, down 606 -> 313; with 128 rows in place of 16 per wave's LDS
-// share, that is with both operands in LDS, the gate/up took 808.
+// 700 rows of one 70B layer, same box: gate/up + SwiGLU 1385 -> 707 us (930 TFLOP/s of the
+// projection), QKV 353 -> 120, O 181 -> 107, down 606 -> 325; with 128 rows in place of 16 per
+// wave's LDS share, that is with both operands in LDS, the gate/up took 808 (this form 685 there).
 constexpr int kBigRows = 128, kBigCols = 256;
 
 // One step's activations of a wave, as operands.

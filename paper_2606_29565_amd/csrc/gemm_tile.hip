@@ -11,12 +11,19 @@
 // 64-element step and the step after next in flight in registers.  An operand read from LDS
 // feeds four products (two row tiles, two halves).  A step takes 1.6 us of a CU; its products
 // alone take 1.3 at the 1.63 PFLOP/s that the matrix cores sustain from registers.
-// 8B shape, same box, against 64-row tiles with the activations in LDS (2467 rows) and 128-row
-// passes over all weights (203 rows): the 64-session pass over 2 layers 5489 -> 5129 us (gate/up
-// + SwiGLU 1043 -> 935 per layer, QKV 238 -> 219, O and down within 2%), the 203-row append over
-// 4 layers 1462 -> 1198 us (gate/up + SwiGLU 150 -> 124, QKV 41 -> 34, O 32 -> 26, down 73 -> 62).
-// 128-column tiles (twice the activation traffic per product) took 1.3-1.4 times as long at 2467
-// rows, and at 128 rows and fewer the passes of gemm.hip stay ahead (166 us per layer, 178 here).
+// 8B shape, us per layer, same box, before (64-row tiles with the activations in LDS; at 203 rows
+// 128-row passes over all weights, SwiGLU apart) and now:
+//                   QKV            O              gate/up + SwiGLU    down
+//   2467 rows   237.0 -> 210.6   161.6 -> 162.5   1035.9 -> 903.4   476.3 -> 464.1
+//   1000 rows    99.7 -> 110.3    58.8 ->  60.6    442.3 -> 381.0   185.0 -> 196.1
+//    600 rows    58.4 ->  60.2    54.3 ->  44.6    322.9 -> 285.7   137.6 -> 127.9
+//    300 rows    34.9 ->  45.3    31.7 ->  31.2    209.8 -> 184.4    92.3 ->  82.9
+//    203 rows    38.8 ->  32.0    28.2 ->  24.1    142.4 -> 112.8    67.4 ->  56.3
+// The larger tile leaves part of the chip idle where 128 x 256 divides badly (QKV at 300 and 1000
+// rows, down at 1000), which gate/up makes up for: the four together are 5-23% faster throughout.
+// 128-column tiles (twice the activation traffic per product) took 1.2-1.4 times as long at 2467
+// rows.  At 128 rows and fewer the passes of gemm.hip stay ahead (128 rows: 166 us per layer, 174
+// with 128-column tiles, 204 with 256).
 #include <algorithm>
 
 #include "common.hpp"
