@@ -140,9 +140,10 @@ __device__ __forceinline__ bool last_arrival(uint32_t* counter, uint32_t total) 
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   return last;
 }
-__device__ __forceinline__ uint32_t* scan_counters(ScanPartial* parts) {
-  return reinterpret_cast<uint32_t*>(parts + k::kScanParts);
+__device__ __forceinline__ uint32_t* scan_counter(ScanPartial* parts, int i) {
+  return reinterpret_cast<uint32_t*>(parts + k::kScanParts) + i * k::kScanCounterWords;
 }
+static_assert(k::kScanCounters * sizeof(ScanPartial) == (k::kScanMax + 1) * k::kScanCounterWords * 4, "");
 __device__ __forceinline__ ScanResult* scan_results(ScanPartial* parts) {
   return reinterpret_cast<ScanResult*>(parts + k::kScanParts + k::kScanCounters);
 }
@@ -272,7 +273,7 @@ __global__ __launch_bounds__(256) void lmhead_kernel(Shape s, const float* __res
     Acc a = from_partial(red[0]);
     for (int w = 1; w < 4; ++w) acc_merge<true>(a, from_partial(red[w]));
     put_record(parts + blockIdx.x, to_partial(a));
-    last = last_arrival(scan_counters(parts), gridDim.x);
+    last = last_arrival(scan_counter(parts, 0), gridDim.x);
   }
   __syncthreads();
   if (!last) return;
@@ -393,7 +394,7 @@ __global__ __launch_bounds__(256) void scan_kernel(int V, J job) {
   a = block_acc<LSE>(a, red);
   if (tid == 0) {
     put_record(job.parts + (int64_t)b * nb + blockIdx.x, to_partial(a));
-    last = last_arrival(scan_counters(job.parts) + b, nb);
+    last = last_arrival(scan_counter(job.parts, b), nb);
   }
   __syncthreads();
   if (!last || tid >= 64) return;
@@ -409,7 +410,7 @@ __global__ __launch_bounds__(256) void scan_kernel(int V, J job) {
     r = make_result<LSE>(a, job.bitmap_of(b), range, job.seq);
     if (n > 1) {
       put_record(scan_results(job.parts) + b, r);
-      final = last_arrival(scan_counters(job.parts) + k::kScanMax, n);
+      final = last_arrival(scan_counter(job.parts, k::kScanMax), n);
     }
   }
   if (!__shfl((int)final, 0, 64)) return;

@@ -167,7 +167,7 @@ def test_gate_latency_single_distribution():
 
 
 @pytest.mark.parametrize("V,n", [(16, 1), (16, 3), (1000, 1), (1008, 64), (4096, 2), (50000, 17),
-                                 (50001, 1), (128256, 63)])
+                                 (50001, 1), (128256, 63), (152064, 16)])
 def test_scan_merges_of_every_launch_shape_and_their_counters(V, n):
     """One block, several blocks and 64 of them per distribution, the scalar path (V % 4 != 0),
     1 to 64 distributions of one launch, called again and again with other values: every call
