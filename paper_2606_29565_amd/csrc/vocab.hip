@@ -7,8 +7,8 @@
 // are dealt to the waves of the whole grid in turn, so that together they read one
 // compact window of W_lm), a butterfly shuffle sums each row, and the same wave keeps
 // a running top-2 (value desc, index asc), a running (max, sum of exp) for the
-// log-sum-exp and a nonfinite flag.  The last workgroup merges the partials of all in a
-// fixed tree order, so the result is deterministic.
+// log-sum-exp and a nonfinite flag.  A second kernel merges the workgroup partials in
+// a fixed tree order, so the result is deterministic.
 //
 // scan: the same reductions over already computed fp32 distributions (the gate's
 // vocabulary scan, and the batched LM head's), one grid column per distribution, merged
@@ -167,11 +167,8 @@ __global__ __launch_bounds__(256) void lmhead_kernel(Shape s, const float* __res
                                                      const T* __restrict__ W,
                                                      const float* __restrict__ bias,
                                                      float* __restrict__ dist,
-                                                     const uint32_t* __restrict__ bitmap,
-                                                     ScanPartial* parts,
-                                                     ScanResult* result, const uint32_t* range) {
+                                                     ScanPartial* parts) {
   __shared__ ScanPartial red[4];
-  __shared__ int last;
   constexpr int E = Elem<T>::kPerFrag;
   const int d = s.d, V = s.vocab;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -272,17 +269,22 @@ __global__ __launch_bounds__(256) void lmhead_kernel(Shape s, const float* __res
   if (tid == 0) {
     Acc a = from_partial(red[0]);
     for (int w = 1; w < 4; ++w) acc_merge<true>(a, from_partial(red[w]));
-    put_record(parts + blockIdx.x, to_partial(a));
-    last = last_arrival(scan_counter(parts, 0), gridDim.x);
+    parts[blockIdx.x] = to_partial(a);
   }
-  __syncthreads();
-  if (!last) return;
-  // the last workgroup merges the partials in a fixed order (so the result does not depend on
-  // which one it is) and writes the session's summary
-  acc_init(acc);
-  for (int b = tid; b < (int)gridDim.x; b += 256) acc_merge<true>(acc, from_partial(get_record(parts + b)));
-  acc = block_acc<true>(acc, red);
-  if (tid == 0) *result = make_result<true>(acc, bitmap, range ? *range : 0u, 1u);
+}
+
+// The LM head's second phase: merges the workgroups' partials in a fixed order and writes the
+// session's summary.
+__global__ __launch_bounds__(256) void lmhead_merge_kernel(const ScanPartial* parts, int nb,
+                                                           ScanResult* result,
+                                                           const uint32_t* bitmap,
+                                                           const uint32_t* range) {
+  __shared__ ScanPartial red[4];
+  Acc a;
+  acc_init(a);
+  for (int b = threadIdx.x; b < nb; b += 256) acc_merge<true>(a, from_partial(parts[b]));
+  a = block_acc<true>(a, red);
+  if (threadIdx.x == 0) *result = make_result<true>(a, bitmap, range ? *range : 0u, 1u);
 }
 
 // What one distribution of a scan needs, from the batch's job or from a job of one (whose
@@ -444,10 +446,10 @@ hipError_t launch_lmhead(const Shape& s, const float* x_row, const void* g_final
 #define SPP_LMHEAD(NCV)                                                                        \
   if (full)                                                                                    \
     SPP_LAUNCH((lmhead_kernel<T, NCV, true>), dim3(nb), dim3(256), 0, st, s, x_row, g, W, bias, \
-               dist, bitmap, parts, result, range);                                            \
+               dist, parts);                                                                   \
   else                                                                                         \
     SPP_LAUNCH((lmhead_kernel<T, NCV, false>), dim3(nb), dim3(256), 0, st, s, x_row, g, W, bias, \
-               dist, bitmap, parts, result, range)
+               dist, parts)
   switch (nc) {
     case 1: SPP_LMHEAD(1); break;
     case 2: SPP_LMHEAD(2); break;
@@ -458,6 +460,7 @@ hipError_t launch_lmhead(const Shape& s, const float* x_row, const void* g_final
     default: return hipErrorInvalidValue;
   }
 #undef SPP_LMHEAD
+  SPP_LAUNCH(lmhead_merge_kernel, dim3(1), dim3(256), 0, st, parts, nb, result, bitmap, range);
   return hipGetLastError();
 }
 
