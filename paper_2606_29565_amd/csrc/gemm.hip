@@ -395,8 +395,11 @@ hipError_t launch_t(const void* X, const void* Xlo, int M, int K, const WeightCa
                     int iters, int row_tiles, float* P, const SwigluOut& so, hipStream_t s) {
   using C = GemmCfg<T, STEPS, NW, MT, CB>;
   const int splits = K / (C::KS * iters), groups = (N + 16 * NW * CB - 1) / (16 * NW * CB);
-  // row tiles: one tile of C::ROWS rows per workgroup
-  if (row_tiles > 0 && (row_tiles != (M + C::ROWS - 1) / C::ROWS || SW)) return hipErrorInvalidValue;
+  // row tiles: one tile of C::ROWS rows per workgroup (and, fused, its rows' sums of
+  // squares staged one per thread)
+  if (row_tiles > 0 && (row_tiles != (M + C::ROWS - 1) / C::ROWS ||
+                        (SW && (C::ROWS * so.nb > C::THREADS || splits != 1))))
+    return hipErrorInvalidValue;
   const dim3 grid = row_tiles > 0 ? dim3((splits * groups + 7) / 8 * 8 * row_tiles, 1)
                                    : dim3(splits, groups);
   SPP_LAUNCH((gemm_kernel<T, STEPS, NW, MT, CB, SW>), grid, dim3(64 * NW), 0, s,
@@ -420,7 +423,8 @@ hipError_t launch_t(const void* X, const void* Xlo, int M, int K, const WeightCa
 #define SPP_GEMM_SWIGLU_SHAPES(X) \
   X(8, 1, 1, 4) X(8, 2, 1, 4) X(8, 4, 1, 4) X(8, 1, 1, 2) X(8, 2, 1, 2) X(8, 4, 1, 2) \
   X(10, 1, 1, 2) X(10, 2, 1, 2) X(12, 1, 1, 2) X(12, 2, 1, 2) X(14, 1, 1, 2) X(14, 2, 1, 2) \
-  X(16, 1, 1, 2) X(16, 2, 1, 2)
+  X(16, 1, 1, 2) X(16, 2, 1, 2) \
+  X(4, 4, 4, 1)
 #endif
 template <typename T, bool SW>
 hipError_t launch(const k::GemmPlan& p, const void* X, const void* Xlo, int M, int K,
@@ -452,7 +456,7 @@ namespace k {
 //     (256) with at least two pipelined slices per workgroup: a second wave of
 //     workgroups, or shorter pipelines, cost more than the idle CUs.
 GemmPlan gemm_plan(const Shape& s, int M, int N, int K) {
-  if (s.bf16 && M > kTileRows) return gemm_plan_tile(M, N, K, true);
+  if (tiled(s, M, N)) return gemm_plan_tile(M, N, K, true);
   GemmPlan p{};
   const int kstep = kStepBytes / (s.bf16 ? 2 : 4);
   const int ksteps = K / kstep;
@@ -516,7 +520,7 @@ GemmPlan gemm_plan(const Shape& s, int M, int N, int K) {
     return p;
   }
   if (M > 256) {
-    // many rows (fp32 models; bf16 ones take gemm_tile.hip): every workgroup runs one 64-row tile over
+    // many rows (fp32 and narrow bf16 projections; see tiled()): every workgroup runs one 64-row tile over
     // the K-range of its split instead of passes over all rows, so each weight byte is read
     // from HBM once per split and shared by the tiles through the XCD's L2; four column
     // blocks per wave make each activation fragment read from LDS feed four matrix-core
@@ -568,7 +572,7 @@ hipError_t gemm(const Shape& s, const GemmPlan& p, const void* X, const void* Xl
                 const WeightCat& w, int N, float* partials, hipStream_t st) {
   if (M <= 0 || p.iters < 1 || (s.bf16 && !Xlo) || w.slab < 1 || (K * (s.bf16 ? 2 : 4) / kStepBytes) % w.slab)
     return hipErrorInvalidValue;
-  if (s.bf16 && M > kTileRows) return gemm_tile(p, X, Xlo, M, K, w, N, partials, st);
+  if (tiled(s, M, N)) return gemm_tile(p, X, Xlo, M, K, w, N, partials, st);
   const SwigluOut none{};
   return s.bf16 ? launch<bf16_t, false>(p, X, Xlo, M, K, w, N, partials, none, st)
                 : launch<float, false>(p, X, Xlo, M, K, w, N, partials, none, st);
@@ -581,13 +585,25 @@ hipError_t gemm(const Shape& s, const GemmPlan& p, const void* X, const void* Xl
 // per CU: rounds of 256 workgroups times the waves of each), 10-16 waves in 2-step slices
 // within 128 registers take the projection in fewer rounds: F = 27648 gives 432 8-wave
 // workgroups (256, then 176 with a third of the CUs idle) or 247 of 14 waves in one round,
-// 8.5% faster.  More rows return splits = 0 (gemm_plan's split-K plan and the SwiGLU kernel) or,
-// past kTileRows in bf16, the fused tile plan.
+// 8.5% faster.  Larger row counts return splits = 0: they take gemm_plan's split-K plan
+// and the SwiGLU kernel.
 GemmPlan gemm_plan_swiglu(const Shape& s, int M, int F, int K) {
   GemmPlan p{};
   const int kstep = kStepBytes / (s.bf16 ? 2 : 4);
   const int ksteps = K / kstep;
-  if (M > kTileRows && s.bf16 && F % 16 == 0) return gemm_plan_tile(M, 2 * F, K, false);
+  if (tiled(s, M, 2 * F) && F % 16 == 0) return gemm_plan_tile(M, 2 * F, K, false);
+  if (M > 256 && s.bf16 && F % 128 == 0 && 64 * res_blocks(s) <= 256) {
+    // many rows: the 64-row tiles of gemm_plan over the full K (the SwiGLU needs every
+    // split's sum), gate and up column blocks on alternate waves as below
+    p.mt = 4;
+    p.nw = 4;
+    p.cb = 4;
+    p.steps = 1;
+    p.iters = ksteps;
+    p.splits = 1;
+    p.row_tiles = (M + 63) / 64;
+    return p;
+  }
   if (M > 64 || F % 16 || M * res_blocks(s) > 512) return p;  // splits = 0: not fused
   p.mt = M <= 16 ? 1 : (M <= 32 ? 2 : 4);
   p.nw = 8;
@@ -617,7 +633,7 @@ hipError_t gemm_swiglu(const Shape& s, const GemmPlan& p, const void* X, const v
   if (M <= 0 || p.splits != 1 || p.iters < 1 || (s.bf16 && !Xlo) || w.slab < 1 ||
       (K * (s.bf16 ? 2 : 4) / kStepBytes) % w.slab || w.nbeg[1] != F || w.nbeg[2] != 2 * F)
     return hipErrorInvalidValue;
-  if (s.bf16 && M > kTileRows) return gemm_tile_swiglu(s, p, X, Xlo, M, K, w, F, ss, act, act_lo, st);
+  if (tiled(s, M, 2 * F)) return gemm_tile_swiglu(s, p, X, Xlo, M, K, w, F, ss, act, act_lo, st);
   const SwigluOut so{ss, res_blocks(s), s.d, s.eps, act, act_lo, F};
   return s.bf16 ? launch<bf16_t, true>(p, X, Xlo, M, K, w, 2 * F, nullptr, so, st)
                 : launch<float, true>(p, X, Xlo, M, K, w, 2 * F, nullptr, so, st);

@@ -219,7 +219,13 @@ int pack_slab_steps_gateup(const Shape& s, int F, int K);
 // The same two projections of bf16 models over more than kTileRows rows (row_tiles tiles of 128
 // rows; splits of whole K-steps, not all alike): gemm_plan, gemm_plan_swiglu, gemm and
 // gemm_swiglu pass them on.  split = false: no K-splits (the fused form).
-constexpr int kTileRows = 128;
+//
+// Only projections at least kTileCols wide: those of the 8B and 32B shapes (N >= 4096; times at
+// the kernel).  With the d = 256 model (N <= 1024) the tiles leave most of the chip idle (4
+// layers, 153 rows: 314 -> 333 us; 30 sessions of up to 44 rows, 1 layer: 255 -> 262), so it
+// keeps the plans of gemm.hip.  Between the two widths nothing was measured.
+constexpr int kTileRows = 128, kTileCols = 1536;
+inline bool tiled(const Shape& s, int M, int N) { return s.bf16 && M > kTileRows && N >= kTileCols; }
 GemmPlan gemm_plan_tile(int M, int N, int K, bool split);
 hipError_t gemm_tile(const GemmPlan& p, const void* X, const void* Xlo, int M, int K,
                      const WeightCat& w, int N, float* partials, hipStream_t st);

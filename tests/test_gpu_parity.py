@@ -548,11 +548,11 @@ def test_stream8b_full_model_every_logit_and_gate():
 @pytest.mark.parametrize("rows", [129, 144, 160, 255, 256, 257, 400])
 def test_many_row_projection_tiles_at_their_edges(rows):
     """The 128-row, 256-column tiles of bf16 projections: a tile of one row, a partly filled wave
-    and a full one, odd numbers of K-steps (d = 320: 5 of 64, F = 448: 7), matrices narrower
-    than a tile and several per tile (Q, K and V): logits and cells against the oracle."""
+    and a full one, odd numbers of K-steps (d = 1600: 25 of 64, F = 832: 13), widths that are no
+    whole tiles, several matrices per tile (Q, K and V): logits and cells against the oracle."""
     import torch
     import paper_2606_29565_amd as spp
-    shape = synth.Shape("tileedge", 2, 320, 5, 1, 64, 448, 2048, 1e4, "bf16")
+    shape = synth.Shape("tileedge", 1, 1600, 25, 5, 64, 832, 2048, 1e4, "bf16")
     seed = 91
     b = build_model(shape, seed, max_tokens=rows)
     toks = synth.cpu_tokens(rows, seed, 0, shape.vocab).tolist()
