@@ -456,7 +456,7 @@ namespace k {
 //     (256) with at least two pipelined slices per workgroup: a second wave of
 //     workgroups, or shorter pipelines, cost more than the idle CUs.
 GemmPlan gemm_plan(const Shape& s, int M, int N, int K) {
-  if (tiled(s, M, N)) return gemm_plan_tile(M, N, K, true);
+  if (tiled(s, M, N) && (M <= 256 || M > kTileMixRows)) return gemm_plan_tile(M, N, K, true);
   GemmPlan p{};
   const int kstep = kStepBytes / (s.bf16 ? 2 : 4);
   const int ksteps = K / kstep;
@@ -520,8 +520,9 @@ GemmPlan gemm_plan(const Shape& s, int M, int N, int K) {
     return p;
   }
   if (M > 256) {
-    // many rows (fp32 and narrow bf16 projections; see tiled()): every workgroup runs one 64-row tile over
-    // the K-range of its split instead of passes over all rows, so each weight byte is read
+    // many rows (fp32 and narrow bf16 projections, and up to kTileMixRows rows the wide ones
+    // where gemm_tile's plan is longer): every workgroup runs one 64-row tile over the
+    // K-range of its split instead of passes over all rows, so each weight byte is read
     // from HBM once per split and shared by the tiles through the XCD's L2; four column
     // blocks per wave make each activation fragment read from LDS feed four matrix-core
     // steps (one or two per read left the projections bound by LDS reads), and the 64-row
@@ -547,6 +548,20 @@ GemmPlan gemm_plan(const Shape& s, int M, int N, int K) {
       if (eff >= 0.85) break;
     }
     p.iters = ksteps / p.splits;
+    if (tiled(s, M, N)) {
+      // The shorter of the two plans: a CU takes 1.45 us per step for two of these tiles and
+      // 1.6 for one of 128 rows, and the partials pass at 6 TB/s (they stay in the memory-side
+      // cache at these sizes).  For QKV, O and down of the 8B shape at 300 rows both estimates
+      // are within 7% of the times at the tile kernel, and the faster side is picked.
+      const GemmPlan t = gemm_plan_tile(M, N, K, true);
+      auto us = [&](int wgs, int round, int steps, double step_us, int splits) {
+        return (double)((wgs + round - 1) / round) * steps * step_us + (double)splits * M * N * 8.0 / 6.0e6;
+      };
+      const double here = us(p.row_tiles * groups * p.splits, 512, p.iters, 1.45, p.splits);
+      const double tile = us(t.row_tiles * groups * t.splits, 256, (ksteps + t.splits - 1) / t.splits, 1.6,
+                             t.splits);
+      if (tile <= here) return t;
+    }
     return p;
   }
   if (p.mt == 8) {
@@ -572,7 +587,7 @@ hipError_t gemm(const Shape& s, const GemmPlan& p, const void* X, const void* Xl
                 const WeightCat& w, int N, float* partials, hipStream_t st) {
   if (M <= 0 || p.iters < 1 || (s.bf16 && !Xlo) || w.slab < 1 || (K * (s.bf16 ? 2 : 4) / kStepBytes) % w.slab)
     return hipErrorInvalidValue;
-  if (tiled(s, M, N)) return gemm_tile(p, X, Xlo, M, K, w, N, partials, st);
+  if (!p.mt) return s.bf16 ? gemm_tile(p, X, Xlo, M, K, w, N, partials, st) : hipErrorInvalidValue;
   const SwigluOut none{};
   return s.bf16 ? launch<bf16_t, false>(p, X, Xlo, M, K, w, N, partials, none, st)
                 : launch<float, false>(p, X, Xlo, M, K, w, N, partials, none, st);
@@ -633,7 +648,8 @@ hipError_t gemm_swiglu(const Shape& s, const GemmPlan& p, const void* X, const v
   if (M <= 0 || p.splits != 1 || p.iters < 1 || (s.bf16 && !Xlo) || w.slab < 1 ||
       (K * (s.bf16 ? 2 : 4) / kStepBytes) % w.slab || w.nbeg[1] != F || w.nbeg[2] != 2 * F)
     return hipErrorInvalidValue;
-  if (tiled(s, M, 2 * F)) return gemm_tile_swiglu(s, p, X, Xlo, M, K, w, F, ss, act, act_lo, st);
+  if (!p.mt)
+    return s.bf16 ? gemm_tile_swiglu(s, p, X, Xlo, M, K, w, F, ss, act, act_lo, st) : hipErrorInvalidValue;
   const SwigluOut so{ss, res_blocks(s), s.d, s.eps, act, act_lo, F};
   return s.bf16 ? launch<bf16_t, true>(p, X, Xlo, M, K, w, 2 * F, nullptr, so, st)
                 : launch<float, true>(p, X, Xlo, M, K, w, 2 * F, nullptr, so, st);

@@ -21,6 +21,7 @@
 //    203 rows    38.8 ->  32.0    28.2 ->  24.1    142.4 -> 112.8    67.4 ->  56.3
 // The larger tile leaves part of the chip idle where 128 x 256 divides badly (QKV at 300 and 1000
 // rows, down at 1000), which gate/up makes up for: the four together are 5-23% faster throughout.
+// At 257-320 rows gemm_plan takes the 64-row tiles where they are estimated shorter (QKV above).
 // 128-column tiles (twice the activation traffic per product) took 1.2-1.4 times as long at 2467
 // rows.  At 128 rows and fewer the passes of gemm.hip stay ahead (128 rows: 166 us per layer, 174
 // with 128-column tiles, 204 with 256).

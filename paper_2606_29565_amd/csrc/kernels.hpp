@@ -224,7 +224,15 @@ int pack_slab_steps_gateup(const Shape& s, int F, int K);
 // the kernel).  With the d = 256 model (N <= 1024) the tiles leave most of the chip idle (4
 // layers, 153 rows: 314 -> 333 us; 30 sessions of up to 44 rows, 1 layer: 255 -> 262), so it
 // keeps the plans of gemm.hip.  Between the two widths nothing was measured.
-constexpr int kTileRows = 128, kTileCols = 1536;
+//
+// From 257 to kTileMixRows rows, where three of its tiles pad to 384 and five of 64 rows to 320,
+// gemm_plan takes the 64-row tiles of gemm.hip for the projections where their estimate is
+// shorter (the 8B QKV; the 32B QKV, O and down).  Appends over 2 layers, 128-row tiles alone and
+// now, one box: 8B 257 rows 809 -> 798 us, 300 817 -> 810; 32B 270 rows 1548 -> 1501, 300
+// 1559 -> 1533.  The same rule beyond gained nothing (8B 350: 843 -> 847, 700: 1376 -> 1404, 1000:
+// 1767 -> 1752; 32B 500: 2080 -> 2085, 900: 3728 -> 3753).
+// A plan of this kernel has mt = 0.
+constexpr int kTileRows = 128, kTileCols = 1536, kTileMixRows = 320;
 inline bool tiled(const Shape& s, int M, int N) { return s.bf16 && M > kTileRows && N >= kTileCols; }
 GemmPlan gemm_plan_tile(int M, int N, int K, bool split);
 hipError_t gemm_tile(const GemmPlan& p, const void* X, const void* Xlo, int M, int K,

@@ -545,7 +545,7 @@ def test_stream8b_full_model_every_logit_and_gate():
     assert decided >= 3 and any(o == spp.SPP_SERVED for o, _ in outcomes.values())
 
 
-@pytest.mark.parametrize("rows", [129, 144, 160, 255, 256, 257, 400])
+@pytest.mark.parametrize("rows", [129, 144, 160, 255, 256, 257, 320, 321, 400])
 def test_many_row_projection_tiles_at_their_edges(rows):
     """The 128-row, 256-column tiles of bf16 projections: a tile of one row, a partly filled wave
     and a full one, odd numbers of K-steps (d = 1600: 25 of 64, F = 832: 13), widths that are no
