@@ -797,12 +797,12 @@ spp_status spp_model_create(const spp_model_config* cfg, const spp_weights* w, s
   }
   dmal((void**)&m->lm_parts, k::kScanBufBytes);
   dmal((void**)&m->gate_parts, k::kScanBufBytes);
-  {
-    const ScanPartial zeros[k::kScanCounters] = {};  // the arrival counters
-    for (ScanPartial* p : {m->lm_parts, m->gate_parts})
-      if (ok && hipMemcpy(p + k::kScanParts, zeros, sizeof(zeros), hipMemcpyHostToDevice) != hipSuccess)
-        ok = false;
-  }
+  // the arrival counters; done when the device is waited for below (two blocking copies of zeros
+  // took about 100 us here)
+  for (ScanPartial* p : {m->lm_parts, m->gate_parts})
+    if (ok && hipMemsetAsync(p + k::kScanParts, 0, k::kScanCounters * sizeof(ScanPartial), nullptr) !=
+                  hipSuccess)
+      ok = false;
   if (ok && hipHostMalloc((void**)&m->gate_host, (k::kScanMax + 1) * sizeof(ScanResult),
                           hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
     ok = false;
