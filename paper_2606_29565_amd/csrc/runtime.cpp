@@ -797,11 +797,12 @@ spp_status spp_model_create(const spp_model_config* cfg, const spp_weights* w, s
   }
   dmal((void**)&m->lm_parts, k::kScanBufBytes);
   dmal((void**)&m->gate_parts, k::kScanBufBytes);
-  // the arrival counters; done when the device is waited for below (two blocking copies of zeros
-  // took about 100 us here)
-  for (ScanPartial* p : {m->lm_parts, m->gate_parts})
-    if (ok && hipMemsetAsync(p + k::kScanParts, 0, k::kScanCounters * sizeof(ScanPartial), nullptr) !=
-                  hipSuccess)
+  // The arrival counters start at zero.  The copies are done when the device is waited for below
+  // (two blocking ones took about 100 us); only batches scan over lm_parts.
+  static const ScanPartial zeros[k::kScanCounters] = {};
+  for (ScanPartial* p : {m->gate_parts, c.max_sessions > 1 ? m->lm_parts : nullptr})
+    if (ok && p && hipMemcpyAsync(p + k::kScanParts, zeros, sizeof(zeros), hipMemcpyHostToDevice, nullptr) !=
+                       hipSuccess)
       ok = false;
   if (ok && hipHostMalloc((void**)&m->gate_host, (k::kScanMax + 1) * sizeof(ScanResult),
                           hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
