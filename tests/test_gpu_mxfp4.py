@@ -2,7 +2,7 @@
 
 The headline model of Sec. 4 is a 70B-class model at 4-bit precision.  The library
 streams its projections as MXFP4 (e2m1 codes, one power-of-two scale per 32 weights along
-K) and dequantizes exactly to bf16 inside the projection kernels.  The oracle
+K) into scaled fp4 x fp6 matrix-core products, which are exact.  The oracle
 dequantizes the same generated bytes itself (``oracle.dequant_mxfp4``) and runs its
 plain forward pass; the GPU logits must match within the pre-position bar."""
 import numpy as np
