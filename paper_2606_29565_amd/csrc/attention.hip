@@ -705,16 +705,6 @@ __global__ __launch_bounds__(64 * kAttnWaves, 1) void attn_kernel_h(
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (s.a6) {  // an MXFP4 model's O projection takes a6 tiles: a lane per (row, 32 dims)
-      constexpr int BPR = DH / 32;
-      for (int b = lane; b < 32 * BPR; b += 64) {
-        const int q = wrow0 + b / BPR;
-        if (q >= R) continue;
-        a6_store(reinterpret_cast<char*>(out), s.n_q * DH / kA6Step, sg.row0 + q / G,
-                 ((it.kvh * G + q % G) * DH) / 32 + b % BPR, t + (b / BPR) * FP + (b % BPR) * 32);
-      }
-      return;
-    }
 #pragma unroll
     for (int i = 0; i < 32; i += RPI) {
       const int q = wrow0 + i + tr;  // the row this lane stores
@@ -838,22 +828,8 @@ __global__ __launch_bounds__(64) void combine_kernel_h(Shape s, StepView sv,
       }
     __syncthreads();  // before the next round overwrites the weights
   }
-  const float inv = 1.f / L;
-  if (s.a6) {  // an MXFP4 model's O projection takes a6 tiles: a lane per (row, 32 dims)
-    constexpr int BPR = DH / 32, FP = DH + 4;
-    __shared__ __attribute__((aligned(16))) float stage[RPB * FP];
-    float* t = stage + sub * FP + li * 8;
-    *reinterpret_cast<float4*>(t) = make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
-    *reinterpret_cast<float4*>(t + 4) = make_float4(acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv);
-    __syncthreads();
-    const int b = threadIdx.x % BPR, rb = blockIdx.y * RPB + threadIdx.x / BPR;
-    const int q = gr.rowgrp * kAttnRowsH + rb;
-    if (threadIdx.x < RPB * BPR && rb < kAttnRowsH && q < R)
-      a6_store(reinterpret_cast<char*>(out), s.n_q * DH / kA6Step, sg.row0 + q / G,
-               ((gr.kvh * G + q % G) * DH) / 32 + b, stage + (threadIdx.x / BPR) * FP + b * 32);
-    return;
-  }
   if (!live) return;
+  const float inv = 1.f / L;
   const int64_t oo = ((int64_t)(sg.row0 + j) * s.n_q + head) * DH + li * 8;
   store_act4(out, out_lo, oo, make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv));
   store_act4(out, out_lo, oo + 4, make_float4(acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv));

@@ -152,6 +152,26 @@ __device__ __forceinline__ f32x4 mma_frag(const uint4& a, const uint4& b, f32x4 
   return c;
 }
 
+// ---- MXFP4 weights: blocks of 16 rows x 128 elements, as pack_weight_fp4 lays them out
+constexpr int kFp4Step = 128;                       // K elements per block
+constexpr int kFp4Code = 1024, kFp4Scale = 64;      // bytes per block
+
+// e8m0 byte J of `s` as an fp32 power of two (2^(E-127); E in [1, 254])
+template <int J>
+__device__ __forceinline__ float e8m0(uint32_t s) {
+  return __uint_as_float(((s >> (8 * J)) & 0xFFu) << 23);
+}
+
+// 8 codes (even k in the low nibbles) and their scale as 8 bf16 weights, the operand of a
+// 16x16x32 product; every e2m1 value times a power of two in range is exact in bf16
+__device__ __forceinline__ uint4 fp4_frag(uint32_t codes, float scale) {
+  return make_uint4(
+      __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(codes, scale, 0)),
+      __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(codes, scale, 1)),
+      __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(codes, scale, 2)),
+      __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(codes, scale, 3)));
+}
+
 // 1 / RMS of row r from its per-block sums of squares.
 __device__ __forceinline__ float row_inv(const float* ss, int r, int nb, int d, float eps) {
   float t = 0.f;
@@ -193,80 +213,6 @@ __device__ __forceinline__ void top2_merge(Top2& t, const Top2& o) {
   t.v2 = ob ? fmaxf(t.v1, o.v2) : fmaxf(t.v2, o.v1);
   t.v1 = ob ? o.v1 : t.v1;
   t.i1 = ob ? o.i1 : t.i1;
-}
-
-// ---- activations of MXFP4 projections ("a6") -------------------------------------------
-//
-// The matrix cores multiply fp4 weights natively, and at the same rate by fp6 as by fp4: four
-// times the bf16 rate.  An activation therefore enters such a product as four fp6 (e2m3)
-// parts with power-of-two scales, x = s (q0 + q1/2^4 + q2/2^9 + q3/2^14): s is the smallest
-// power of two with |x| <= 7.75 s over 32 consecutive elements, and the steps between the
-// parts are what the rounding of the part before leaves (at most 0.25, then 0.125, of a range
-// of 4).  Against the exact value the four parts are off by 1.0e-6 of the 2-norm for normal
-// values and 1.7e-6 for SwiGLU outputs; the two bf16 halves that the bf16 projections take
-// are off by 2.4e-6.
-//
-// Layout: per 16 rows x 128 elements one tile of kA6Tile bytes: for each part 64 units of 16
-// bytes (the first four dwords of a lane's 192-bit operand), then for each part 64 units of 8
-// bytes (the other two), then 64 dwords with the four parts' e8m0 scales.  Lane 16 g + r (row
-// r, elements 32 g .. 32 g + 31) finds its data in unit a6_unit(r, g): a row's units are
-// adjacent (the producers write them row by row), and the 16 rows of one g fall on distinct
-// LDS banks.  Tiles are ordered [row tile][K-step].
-constexpr int kA6Step = 128;     // elements along K per tile
-constexpr int kA6Tile = 6400;    // bytes
-constexpr int kA6Low = 4096;     // offset of the 8-byte units
-constexpr int kA6Scale = 6144;   // offset of the scales
-constexpr int kA6Pitch = 36;     // floats between the 32-element blocks staged in LDS
-
-__device__ __forceinline__ int a6_unit(int r, int g) { return 4 * r + (g ^ (r >> 2)); }
-
-// Writes 32 consecutive activations (block `blk` of row `row`) read from `src` (16-byte
-// aligned, in LDS).  A block with a NaN or an infinity gets NaN scales, so every product of
-// the row is NaN as it was with the value itself.
-__device__ __forceinline__ void a6_store(char* A, int ksteps, int row, int blk, const float* src) {
-  typedef float f32x16v __attribute__((ext_vector_type(16)));
-  typedef float f32x32v __attribute__((ext_vector_type(32)));
-  f32x16v even, odd;
-  float mx = 0.f, bad = 0.f;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const float4 v = *reinterpret_cast<const float4*>(src + 4 * i);
-    even[2 * i] = v.x;
-    odd[2 * i] = v.y;
-    even[2 * i + 1] = v.z;
-    odd[2 * i + 1] = v.w;
-    mx = fmaxf(fmaxf(mx, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
-    bad += v.x * 0.f + v.y * 0.f + v.z * 0.f + v.w * 0.f;  // NaN iff a value is not finite
-  }
-  // smallest power of two >= mx / 7.75, at least 2^-112 so that the last part's scale is one
-  int e = (int)((__float_as_uint(mx * (1.f / 7.75f)) + 0x7FFFFFu) >> 23);
-  e = e < 15 ? 15 : e;
-  const int g = blk & 3, r = row & 15, u = a6_unit(r, g);
-  char* t = A + ((int64_t)(row >> 4) * ksteps + (blk >> 2)) * kA6Tile;
-  constexpr int kDrop[4] = {0, 4, 9, 14};
-#pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    float sc = __uint_as_float((uint32_t)(e - kDrop[p]) << 23);
-    // (elements 2i from the first operand, 2i + 1 from the second)  These conversions write
-    // their first results before they have read their last operands, and the compiler does not
-    // keep the two apart: the empty statements hold the operands in place until after them.
-    asm volatile("" : "+v"(even), "+v"(odd), "+v"(sc));
-    const auto q = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(even, odd, sc);
-    asm volatile("" : : "v"(even), "v"(odd), "v"(sc), "v"(q));
-    *reinterpret_cast<uint4*>(t + p * 1024 + u * 16) = make_uint4(q[0], q[1], q[2], q[3]);
-    *reinterpret_cast<uint2*>(t + kA6Low + p * 512 + u * 8) = make_uint2(q[4], q[5]);
-    if (p < 3) {
-      const f32x32v back = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(q, sc);
-      asm volatile("" : : "v"(q), "v"(sc), "v"(back));
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        even[i] -= back[2 * i];
-        odd[i] -= back[2 * i + 1];
-      }
-    }
-  }
-  const uint32_t scales = e | ((e - 4) << 8) | ((e - 9) << 16) | ((uint32_t)(e - 14) << 24);
-  *reinterpret_cast<uint32_t*>(t + kA6Scale + u * 4) = bad == 0.f ? scales : 0xFFFFFFFFu;
 }
 
 // x + P[0][off] + P[1][off] + ... + P[splits-1][off] (float4 at element offset `off`,

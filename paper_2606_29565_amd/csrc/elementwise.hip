@@ -27,25 +27,14 @@ __device__ __forceinline__ float block_sum_256(float v, float* red) {
   return red[0] + red[1] + red[2] + red[3];
 }
 
-// Columns c0 .. c0 + 1023 of row `row` (4 consecutive ones per thread of the 256) as a6 tiles:
-// gathered in LDS, then a lane per 32-element block.
-__device__ __forceinline__ void store_a6_row(char* A, int d, int row, int c0, float4 v, float* buf) {
-  const int tid = threadIdx.x;
-  *reinterpret_cast<float4*>(buf + (tid >> 3) * kA6Pitch + (tid & 7) * 4) = v;
-  __syncthreads();
-  if (tid < 32 && c0 + tid * 32 < d)
-    a6_store(A, d / kA6Step, row, c0 / 32 + tid, buf + tid * kA6Pitch);
-}
-
 // Grid (rows, blocks of 1024 columns): x[r] = E[token[r]] (fp32), y[r] = x[r] * g in the
 // (hi, lo) split, ss[r][block] = sum of x^2 over the block; block 0 also writes the
 // rotary table of row r: (cos, sin) of pos[r] * base^(-2i/dh), angles in double.
-template <typename T, bool A6>
+template <typename T>
 __global__ __launch_bounds__(256) void embed_kernel(Shape s, StepView sv, const T* E,
                                                     const T* g, float* x, T* y, T* y_lo,
                                                     float* ss, uint32_t* range) {
   __shared__ float red[4];
-  __shared__ __attribute__((aligned(16))) float buf[A6 ? 32 * kA6Pitch : 4];
   const int r = blockIdx.x, blk = blockIdx.y, d = s.d;
   // the step's range words start clear (every later kernel of the step orders after this)
   if (r == 0 && blk == 0)
@@ -53,17 +42,15 @@ __global__ __launch_bounds__(256) void embed_kernel(Shape s, StepView sv, const 
   const int tok = sv.token[r];
   const int c = blk * 1024 + threadIdx.x * 4;
   float q = 0.f;
-  float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
   if (c < d) {
     const T* er = E + (int64_t)tok * d + c;
     const float4 v = make_float4(load_elem(er, 0), load_elem(er, 1), load_elem(er, 2), load_elem(er, 3));
     *reinterpret_cast<float4*>(x + (int64_t)r * d + c) = v;
-    o = make_float4(v.x * load_elem(g, c), v.y * load_elem(g, c + 1), v.z * load_elem(g, c + 2),
-                    v.w * load_elem(g, c + 3));
-    if constexpr (!A6) store_act4(y, y_lo, (int64_t)r * d + c, o);
+    store_act4(y, y_lo, (int64_t)r * d + c,
+               make_float4(v.x * load_elem(g, c), v.y * load_elem(g, c + 1), v.z * load_elem(g, c + 2),
+                           v.w * load_elem(g, c + 3)));
     q = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
   }
-  if constexpr (A6) store_a6_row(reinterpret_cast<char*>(y), d, r, blk * 1024, o, buf);
   q = block_sum_256(q, red);
   if (threadIdx.x == 0) ss[(int64_t)r * gridDim.y + blk] = q;
 }
@@ -195,30 +182,24 @@ __global__ __launch_bounds__(64) void qkv_epilogue_kernel(Shape s, StepView sv, 
 // Grid (rows, blocks of 1024 columns): x[r] += sum over splits of P[split][r] (added in
 // split order, every split's load in flight at once); if g is given, y[r] = x[r] * g in
 // the (hi, lo) split; ss[r][block] = sum of x^2 over the block.
-template <typename T, bool A6>
+template <typename T>
 __global__ __launch_bounds__(256) void residual_kernel(Shape s, int M, const float* P, int splits,
                                                        float* x, const T* g, T* y, T* y_lo,
                                                        float* ss) {
   __shared__ float red[4];
-  __shared__ __attribute__((aligned(16))) float buf[A6 ? 32 * kA6Pitch : 4];
   const int r = blockIdx.x, blk = blockIdx.y, d = s.d;
   float* xr = x + (int64_t)r * d;
   const int c = blk * 1024 + threadIdx.x * 4;
   float q = 0.f;
-  float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
   if (c < d) {
     float4 v = *reinterpret_cast<const float4*>(xr + c);
     v = add_splits4(v, P, (int64_t)M * d, splits, (int64_t)r * d + c);
     *reinterpret_cast<float4*>(xr + c) = v;
-    if (g) {
-      o = make_float4(v.x * load_elem(g, c), v.y * load_elem(g, c + 1), v.z * load_elem(g, c + 2),
-                      v.w * load_elem(g, c + 3));
-      if constexpr (!A6) store_act4(y, y_lo, (int64_t)r * d + c, o);
-    }
+    if (g)
+      store_act4(y, y_lo, (int64_t)r * d + c,
+                 make_float4(v.x * load_elem(g, c), v.y * load_elem(g, c + 1),
+                             v.z * load_elem(g, c + 2), v.w * load_elem(g, c + 3)));
     q = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-  }
-  if constexpr (A6) {
-    if (g) store_a6_row(reinterpret_cast<char*>(y), d, r, blk * 1024, o, buf);  // (uniform)
   }
   q = block_sum_256(q, red);
   if (threadIdx.x == 0) ss[(int64_t)r * gridDim.y + blk] = q;
@@ -247,27 +228,6 @@ __global__ __launch_bounds__(256) void swiglu_kernel(Shape s, int M, const float
                                  a.z / (1.f + __expf(-a.z)) * b.z, a.w / (1.f + __expf(-a.w)) * b.w);
     store_act4(act, act_lo, t * 4, o);
   }
-}
-
-// The same for a6 output: grid (rows, blocks of 1024 columns), four columns per thread.
-template <int S>
-__global__ __launch_bounds__(256) void swiglu_a6_kernel(Shape s, int M, const float* P, int splits,
-                                                        const float* ss, int nb, char* act) {
-  __shared__ __attribute__((aligned(16))) float buf[32 * kA6Pitch];
-  const int F = s.ffn, r = blockIdx.x, c0 = blockIdx.y * 1024, f = c0 + threadIdx.x * 4;
-  const int64_t N = 2 * (int64_t)F;
-  const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-  float4 o = z;
-  if (f < F) {
-    const float inv = row_inv(ss, r, nb, s.d, s.eps);
-    float4 a = add_splits4_n<S>(z, P, (int64_t)M * N, splits, r * N + f);
-    float4 b = add_splits4_n<S>(z, P, (int64_t)M * N, splits, r * N + F + f);
-    a = make_float4(a.x * inv, a.y * inv, a.z * inv, a.w * inv);
-    b = make_float4(b.x * inv, b.y * inv, b.z * inv, b.w * inv);
-    o = make_float4(a.x / (1.f + __expf(-a.x)) * b.x, a.y / (1.f + __expf(-a.y)) * b.y,
-                    a.z / (1.f + __expf(-a.z)) * b.z, a.w / (1.f + __expf(-a.w)) * b.w);
-  }
-  store_a6_row(act, F, r, c0, o, buf);
 }
 
 // z[i] = rmsnorm(x[last row of segment i]) * g_final, in the model dtype.
@@ -463,16 +423,12 @@ hipError_t embed(const Shape& s, const StepView& dp, int n_rows, const void* emb
                  hipStream_t st) {
   if (s.d % 4) return hipErrorInvalidValue;
   dim3 grid(n_rows, res_blocks(s));
-  if (s.a6)
-    SPP_LAUNCH((embed_kernel<bf16_t, true>), grid, dim3(256), 0, st, s, dp,
-                       static_cast<const bf16_t*>(emb), static_cast<const bf16_t*>(g), x,
-                       static_cast<bf16_t*>(y), static_cast<bf16_t*>(y_lo), ss, range);
-  else if (s.bf16)
-    SPP_LAUNCH((embed_kernel<bf16_t, false>), grid, dim3(256), 0, st, s, dp,
+  if (s.bf16)
+    SPP_LAUNCH(embed_kernel<bf16_t>, grid, dim3(256), 0, st, s, dp,
                        static_cast<const bf16_t*>(emb), static_cast<const bf16_t*>(g), x,
                        static_cast<bf16_t*>(y), static_cast<bf16_t*>(y_lo), ss, range);
   else
-    SPP_LAUNCH((embed_kernel<float, false>), grid, dim3(256), 0, st, s, dp,
+    SPP_LAUNCH(embed_kernel<float>, grid, dim3(256), 0, st, s, dp,
                        static_cast<const float*>(emb), static_cast<const float*>(g), x,
                        static_cast<float*>(y), static_cast<float*>(y_lo), ss, range);
   SPP_LAUNCH(rope_kernel, dim3(n_rows), dim3(64), 0, st, s, dp, rope);
@@ -507,16 +463,12 @@ hipError_t residual(const Shape& s, int n_rows, const float* partials, int split
                     const void* g, void* y, void* y_lo, float* ss, hipStream_t st) {
   if (s.d % 4) return hipErrorInvalidValue;
   dim3 grid(n_rows, res_blocks(s));
-  if (s.a6)
-    SPP_LAUNCH((residual_kernel<bf16_t, true>), grid, dim3(256), 0, st, s, n_rows, partials, splits,
-                       x, static_cast<const bf16_t*>(g), static_cast<bf16_t*>(y),
-                       static_cast<bf16_t*>(y_lo), ss);
-  else if (s.bf16)
-    SPP_LAUNCH((residual_kernel<bf16_t, false>), grid, dim3(256), 0, st, s, n_rows, partials, splits,
+  if (s.bf16)
+    SPP_LAUNCH(residual_kernel<bf16_t>, grid, dim3(256), 0, st, s, n_rows, partials, splits,
                        x, static_cast<const bf16_t*>(g), static_cast<bf16_t*>(y),
                        static_cast<bf16_t*>(y_lo), ss);
   else
-    SPP_LAUNCH((residual_kernel<float, false>), grid, dim3(256), 0, st, s, n_rows, partials, splits,
+    SPP_LAUNCH(residual_kernel<float>, grid, dim3(256), 0, st, s, n_rows, partials, splits,
                        x, static_cast<const float*>(g), static_cast<float*>(y),
                        static_cast<float*>(y_lo), ss);
   return hipGetLastError();
@@ -529,20 +481,6 @@ hipError_t swiglu(const Shape& s, int n_rows, const float* partials, int splits,
   const int64_t total = (int64_t)n_rows * s.ffn / 4;
   int64_t blocks = (total + 255) / 256;
   if (blocks > 4096) blocks = 4096;
-  if (s.a6) {
-    const dim3 grid(n_rows, (s.ffn + 1023) / 1024);
-#define SPP_SWI6(S)                                                                     \
-  SPP_LAUNCH((swiglu_a6_kernel<S>), grid, dim3(256), 0, st, s, n_rows, partials, splits, ss, nb, \
-             static_cast<char*>(act))
-    switch (split_bucket(splits)) {
-      case 4: SPP_SWI6(4); break;
-      case 8: SPP_SWI6(8); break;
-      case 16: SPP_SWI6(16); break;
-      default: SPP_SWI6(0); break;
-    }
-#undef SPP_SWI6
-    return hipGetLastError();
-  }
 #define SPP_SWI(T, S)                                                                          \
   SPP_LAUNCH((swiglu_kernel<T, S>), dim3((unsigned)blocks), dim3(256), 0, st, s, n_rows,       \
              partials, splits, ss, nb, static_cast<T*>(act), static_cast<T*>(act_lo))

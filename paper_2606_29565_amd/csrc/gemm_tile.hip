@@ -1,4 +1,4 @@
-// Projections of bf16 models over many rows (more than 128):
+// Projections over many rows (more than 128), of bf16 and of MXFP4 weights:
 //   P[split][M][N] = X[M][K-range of split] . W[N][K-range]^T,  X = hi + lo
 // where the products, not the weight stream, bound the kernel: every weight meets two bf16
 // halves of each activation.
@@ -22,6 +22,10 @@
 // The larger tile leaves part of the chip idle where 128 x 256 divides badly (QKV at 300 and 1000
 // rows, down at 1000), which gate/up makes up for: the four together are 5-23% faster throughout.
 // At 257-320 rows gemm_plan takes the 64-row tiles where they are estimated shorter (QKV above).
+// MXFP4 weights take the same tiles: a block of codes holds two steps, and the wave that brings
+// it in makes the bf16 operands on the way to LDS.  Appends over 3 layers of the 70B shape, us,
+// 128-row passes over all weights and now: 129 rows 2558 -> 2384, 300 rows 3998 -> 3331, 700 rows
+// 8216 -> 6428, 1100 rows 12615 -> 11485.
 // 128-column tiles (twice the activation traffic per product) took 1.2-1.4 times as long at 2467
 // rows.  At 128 rows and fewer the passes of gemm.hip stay ahead (128 rows: 166 us per layer, 174
 // with 128-column tiles, 204 with 256).
@@ -48,7 +52,8 @@ struct SwigluTile {
 };
 
 struct TileBlock {
-  const char* base;  // the matrix
+  const char* base;   // the matrix (bf16 blocks, or MXFP4 codes)
+  const char* scale;  // its MXFP4 scales
   int cb, nblk;
 };
 __device__ __forceinline__ TileBlock tile_block(const WeightCat& w, int n) {
@@ -56,10 +61,24 @@ __device__ __forceinline__ TileBlock tile_block(const WeightCat& w, int n) {
   const int nn = n < w.nbeg[3] ? n : 0;
   const int mi = nn >= w.nbeg[2] ? 2 : (nn >= w.nbeg[1] ? 1 : 0);
   const void* mat = mi == 2 ? w.mat[2] : (mi == 1 ? w.mat[1] : w.mat[0]);
+  const void* scale = mi == 2 ? w.scale[2] : (mi == 1 ? w.scale[1] : w.scale[0]);
   const int nb = mi == 2 ? w.nbeg[2] : (mi == 1 ? w.nbeg[1] : w.nbeg[0]);
   const int ne = mi == 2 ? w.nbeg[3] : (mi == 1 ? w.nbeg[2] : w.nbeg[1]);
-  return TileBlock{static_cast<const char*>(mat), (nn - nb) / 16, (ne - nb) / 16};
+  return TileBlock{static_cast<const char*>(mat), static_cast<const char*>(scale), (nn - nb) / 16,
+                   (ne - nb) / 16};
 }
+
+// The weights that a wave brings in for one step: both operands of its blocks, or (MXFP4) the
+// codes and scales of the blocks that hold the step, whose operands are made on the way to LDS.
+template <bool Q4, int PER>
+struct TileWeights {
+  uint4 f[PER][2];
+};
+template <int PER>
+struct TileWeights<true, PER> {
+  uint4 code[PER];
+  uint32_t scale[PER];
+};
 
 // c[n][row] += W[n][k] x[row][k] over 32 elements: lane 16 g + r holds weight row r and
 // activation row r at k = 8 g + 0..7; c is weight rows 4 g .. 4 g + 3 of activation row r.
@@ -67,7 +86,7 @@ __device__ __forceinline__ f32x4 mma(const uint4& w, const uint4& x, f32x4 c) {
   return mma_frag(w, x, c, bf16_t{});
 }
 
-template <bool SW>
+template <bool SW, bool Q4>
 __global__ __launch_bounds__(256, 2) void tile_kernel(const bf16_t* __restrict__ X,
                                                       const bf16_t* __restrict__ Xlo, int M, int K,
                                                       WeightCat w, int N, float* __restrict__ P,
@@ -88,8 +107,11 @@ __global__ __launch_bounds__(256, 2) void tile_kernel(const bf16_t* __restrict__
   const int xy = in / band * 8 + xcd, tile_m = rb * band + in % band;
   if (xy >= splits * groups || tile_m >= row_tiles) return;
   const int split = xy % splits, cgroup = xy / splits;
-  const int ksteps = K / kStep;
-  const int k0 = (int)((int64_t)split * ksteps / splits), k1 = (int)((int64_t)(split + 1) * ksteps / splits);
+  // the stored blocks: one step each, or (MXFP4) two
+  constexpr int SPB = Q4 ? kFp4Step / kStep : 1;
+  const int kblocks = K / (kStep * SPB);
+  const int b0 = (int)((int64_t)split * kblocks / splits), b1 = (int)((int64_t)(split + 1) * kblocks / splits);
+  const int k0 = b0 * SPB, k1 = b1 * SPB;
   const int row0 = tile_m * kRows + wave * 32;
 
   auto column = [&](int b) {  // first column of block b, in the concatenated matrices
@@ -106,20 +128,25 @@ __global__ __launch_bounds__(256, 2) void tile_kernel(const bf16_t* __restrict__
 
   // Both operands are walked step by step: uniform bases that advance, and offsets that stay.
   // Past the range the last step is loaded again and never used.
-  const int nslab = ksteps / w.slab;
-  int ts = k0 % w.slab, sl = k0 / w.slab, pos = ts * nslab + sl;  // (time-major position)
-  int wleft = k1 - k0, aleft = k1 - k0;
-  struct Weights {
-    uint4 f[PER][2];
-  };
+  const int nslab = kblocks / w.slab;
+  int ts = b0 % w.slab, sl = b0 / w.slab, pos = ts * nslab + sl;  // (time-major position)
+  int wleft = b1 - b0, aleft = k1 - k0;
+  using Weights = TileWeights<Q4, PER>;
+  bool second = false, second_st = false;  // (MXFP4) the half of its block that comes next
   auto load_w = [&](Weights& x) {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      const char* p = blk[i].base + ((int64_t)pos * blk[i].nblk + blk[i].cb) * kBlock + (uint32_t)lane * 16;
-      x.f[i][0] = ld_global(p);
-      x.f[i][1] = ld_global(p + 1024);
+      const int64_t p = (int64_t)pos * blk[i].nblk + blk[i].cb;
+      if constexpr (Q4) {
+        x.code[i] = ld_global(blk[i].base + p * kFp4Code + (uint32_t)lane * 16);
+        x.scale[i] = ld_global_u32(blk[i].scale + p * kFp4Scale + (uint32_t)r * 4);
+      } else {
+        x.f[i][0] = ld_global(blk[i].base + p * kBlock + (uint32_t)lane * 16);
+        x.f[i][1] = ld_global(blk[i].base + p * kBlock + (uint32_t)lane * 16 + 1024);
+      }
     }
-    const bool go = wleft > 1, wrap = ts + 1 == w.slab;
+    const bool go = wleft > 1 && (!Q4 || second), wrap = ts + 1 == w.slab;
+    second = !second;
     wleft -= go ? 1 : 0;
     sl += go && wrap ? 1 : 0;
     pos = go ? (wrap ? sl : pos + nslab) : pos;
@@ -129,9 +156,17 @@ __global__ __launch_bounds__(256, 2) void tile_kernel(const bf16_t* __restrict__
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       char* p = buf + (wave + i * NW) * kBlock + lane * 16;
-      *reinterpret_cast<uint4*>(p) = x.f[i][0];
-      *reinterpret_cast<uint4*>(p + 1024) = x.f[i][1];
+      if constexpr (Q4) {
+        const uint32_t c0 = second_st ? x.code[i].z : x.code[i].x, c1 = second_st ? x.code[i].w : x.code[i].y;
+        const uint32_t sc = second_st ? x.scale[i] >> 16 : x.scale[i];
+        *reinterpret_cast<uint4*>(p) = fp4_frag(c0, e8m0<0>(sc));
+        *reinterpret_cast<uint4*>(p + 1024) = fp4_frag(c1, e8m0<1>(sc));
+      } else {
+        *reinterpret_cast<uint4*>(p) = x.f[i][0];
+        *reinterpret_cast<uint4*>(p + 1024) = x.f[i][1];
+      }
     }
+    second_st = !second_st;
   };
   struct Act {
     uint4 x[2][2][2];  // [operand of 32 elements][row tile][hi, lo]
@@ -238,15 +273,26 @@ __global__ __launch_bounds__(256, 2) void tile_kernel(const bf16_t* __restrict__
   }
 }
 
-template <bool SW>
-hipError_t launch(const k::GemmPlan& p, const void* X, const void* Xlo, int M, int K, const WeightCat& w,
-                  int N, float* P, const SwigluTile& so, hipStream_t st) {
+template <bool SW, bool Q4>
+hipError_t launch_t(const k::GemmPlan& p, const void* X, const void* Xlo, int M, int K, const WeightCat& w,
+                    int N, float* P, const SwigluTile& so, hipStream_t st) {
   const int groups = (N + 16 * CB - 1) / (16 * CB), band = std::min(p.row_tiles, 8);
   const int bands = (p.row_tiles + band - 1) / band, octs = (p.splits * groups + 7) / 8;
-  SPP_LAUNCH((tile_kernel<SW>), dim3((unsigned)(bands * band * octs * 8)), dim3(256), 0, st,
+  SPP_LAUNCH((tile_kernel<SW, Q4>), dim3((unsigned)(bands * band * octs * 8)), dim3(256), 0, st,
              static_cast<const bf16_t*>(X), static_cast<const bf16_t*>(Xlo), M, K, w, N, P, so, p.splits,
              groups, p.row_tiles, band);
   return hipGetLastError();
+}
+template <bool SW>
+hipError_t launch(const k::GemmPlan& p, const void* X, const void* Xlo, int M, int K, const WeightCat& w,
+                  int N, float* P, const SwigluTile& so, hipStream_t st) {
+  const bool q4 = w.scale[0] != nullptr;
+  const int blocks = K / (q4 ? kFp4Step : kStep);  // stored blocks along K: what the splits divide
+  if (M <= 0 || p.row_tiles != (M + kRows - 1) / kRows || K % (q4 ? kFp4Step : kStep) || p.splits < 1 ||
+      p.splits > blocks || w.slab < 1 || blocks % w.slab)
+    return hipErrorInvalidValue;
+  return q4 ? launch_t<SW, true>(p, X, Xlo, M, K, w, N, P, so, st)
+            : launch_t<SW, false>(p, X, Xlo, M, K, w, N, P, so, st);
 }
 
 }  // namespace
@@ -276,18 +322,14 @@ GemmPlan gemm_plan_tile(int M, int N, int K, bool split) {
 
 hipError_t gemm_tile(const GemmPlan& p, const void* X, const void* Xlo, int M, int K,
                      const WeightCat& w, int N, float* partials, hipStream_t st) {
-  if (p.row_tiles != (M + kRows - 1) / kRows || K % kStep || p.splits < 1 || p.splits > K / kStep ||
-      w.nbeg[3] != N)
-    return hipErrorInvalidValue;
+  if (w.nbeg[3] != N) return hipErrorInvalidValue;
   return launch<false>(p, X, Xlo, M, K, w, N, partials, SwigluTile{}, st);
 }
 
 hipError_t gemm_tile_swiglu(const Shape& s, const GemmPlan& p, const void* X, const void* Xlo, int M,
                             int K, const WeightCat& w, int F, const float* ss, void* act, void* act_lo,
                             hipStream_t st) {
-  if (p.row_tiles != (M + kRows - 1) / kRows || K % kStep || p.splits != 1 || F % 16 ||
-      w.nbeg[1] != F || w.nbeg[3] != 2 * F)
-    return hipErrorInvalidValue;
+  if (p.splits != 1 || F % 16 || w.nbeg[1] != F || w.nbeg[3] != 2 * F) return hipErrorInvalidValue;
   const SwigluTile so{ss, res_blocks(s), s.d, s.eps, static_cast<bf16_t*>(act),
                       static_cast<bf16_t*>(act_lo), F};
   return launch<true>(p, X, Xlo, M, K, w, 2 * F, nullptr, so, st);

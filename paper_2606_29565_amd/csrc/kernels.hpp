@@ -121,7 +121,6 @@ struct Shape {
   float eps;
   double rope_base;
   int32_t bf16;
-  int32_t a6;  // MXFP4 projections: their inputs are stored as a6 tiles (see common.hpp)
 };
 
 // Query rows per attention row group of a model.
@@ -169,8 +168,7 @@ namespace k {
 
 // Matrix-core inputs (h, attention output, SwiGLU output, final-norm rows) are written
 // as a (hi, lo) pair of arrays in bf16 models (lo = bf16 rounding remainder; the GEMM
-// multiplies both); fp32 models use hi alone; MXFP4 models store a6 tiles in its place (the
-// lo pointers are unused).
+// multiplies both); fp32 models use hi alone.
 
 // RMSNorm is factored: (RMSNorm(x) * g) W = inv * ((x * g) W), inv[r] = 1/sqrt(mean(x[r]^2)
 // + eps).  Producers of x write y = x * g (the projection input) and ss[r][b], the sums of
@@ -251,23 +249,18 @@ hipError_t pack_weight(int elem_bytes, const void* src, void* dst, int N, int K,
                        hipStream_t st);
 
 // MXFP4 projections (4-bit e2m1 weights, one e8m0 scale per 32 along K; bf16 models):
-// the same partials as gemm() from the tiled codes and scales of pack_weight_fp4 and a6
-// activations (X; the lo argument is unused).  K is a multiple of 128 (one step); `slab`
-// counts steps.
+// the same partials as gemm() from the tiled codes and scales of pack_weight_fp4.  K is
+// a multiple of 128 (one step); `slab` counts steps.
 GemmPlan gemm_plan_fp4(const Shape& s, int M, int N, int K);
 int pack_slab_steps_fp4(const Shape& s, int N, int K);
 hipError_t gemm_fp4(const Shape& s, const GemmPlan& p, const void* X, const void* Xlo, int M, int K,
                     const WeightCat& w, int N, float* partials, hipStream_t st);
-// The fused gate/up + SwiGLU over MXFP4 gate and up matrices (as gemm_swiglu; act in a6).
+// The fused gate/up + SwiGLU over MXFP4 gate and up matrices (as gemm_swiglu).
 GemmPlan gemm_plan_swiglu_fp4(const Shape& s, int M, int F, int K);
 hipError_t gemm_swiglu_fp4(const Shape& s, const GemmPlan& p, const void* X, const void* Xlo, int M,
                            int K, const WeightCat& w, int F, const float* ss, void* act,
                            void* act_lo, hipStream_t st);
 int pack_slab_steps_gateup_fp4(const Shape& s, int F, int K);
-// Bytes of the a6 tiles (16 rows x 128 elements: 6400 bytes) of `rows` rows of `cols` elements.
-inline size_t a6_bytes(int rows, int cols) {
-  return (size_t)((rows + 15) / 16) * (size_t)(cols / 128) * 6400;
-}
 // Row-major codes [N][K/2] (even k in the low nibble) and scales [N][K/32] into the tiled
 // layout: per 16 rows x 128 columns a 1 KB code block (lane order of the MFMA B
 // fragments) and a 64-byte scale block, ordered time-major with `slab` steps per slab.

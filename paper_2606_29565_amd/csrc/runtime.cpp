@@ -635,8 +635,7 @@ int fp4_slab(const Shape& s, int which) {
 
 Shape shape_of(const spp_model_config& c) {
   return Shape{c.n_layers, c.d_model, c.n_q_heads, c.n_kv_heads, c.head_dim, c.ffn_dim, c.vocab,
-               c.rms_eps, c.rope_base, c.dtype == SPP_DTYPE_BF16 ? 1 : 0,
-               c.weight_format == SPP_WFMT_MXFP4 ? 1 : 0};
+               c.rms_eps, c.rope_base, c.dtype == SPP_DTYPE_BF16 ? 1 : 0};
 }
 
 }  // namespace
@@ -734,14 +733,10 @@ spp_status spp_model_create(const spp_model_config* cfg, const spp_weights* w, s
     if (ok && hipMalloc(p, b) != hipSuccess) ok = false;
   };
   dmal((void**)&m->x, Mx * s.d * 4);
-  // projection inputs: (hi, lo) arrays, or the a6 tiles of MXFP4 models
-  auto act_bytes = [&](int cols) {
-    return s.a6 ? k::a6_bytes(c.max_tokens, cols) : 2 * Mx * cols * m->elem;
-  };
-  dmal(&m->h, act_bytes(s.d));
+  dmal(&m->h, 2 * Mx * s.d * m->elem);      // hi, lo
   dmal(&m->q, 2 * Mx * nq * m->elem);       // hi, lo
-  dmal(&m->att, act_bytes(nq));
-  dmal(&m->act, act_bytes(s.ffn));
+  dmal(&m->att, 2 * Mx * nq * m->elem);     // hi, lo
+  dmal(&m->act, 2 * Mx * s.ffn * m->elem);  // hi, lo
   dmal((void**)&m->part, part_elems * 4);
   dmal((void**)&m->ss, Mx * k::res_blocks(s) * 4);
   dmal((void**)&m->range, kMaxSegments * sizeof(uint32_t));

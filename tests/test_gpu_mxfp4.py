@@ -2,9 +2,9 @@
 
 The headline model of Sec. 4 is a 70B-class model at 4-bit precision.  The library
 streams its projections as MXFP4 (e2m1 codes, one power-of-two scale per 32 weights along
-K) into scaled fp4 x fp6 matrix-core products, which are exact.  The oracle
-dequantizes the same generated bytes itself (``oracle.dequant_mxfp4``) and runs its
-plain forward pass; the GPU logits must match within the pre-position bar."""
+K) and dequantizes them exactly to bf16 in registers.  The oracle dequantizes the same
+generated bytes itself (``oracle.dequant_mxfp4``) and runs its plain forward pass; the
+GPU logits must match within the pre-position bar."""
 import numpy as np
 import pytest
 
@@ -216,8 +216,8 @@ def test_mxfp4_rows_at_the_edges_of_the_projection_tiles(rows):
 @pytest.mark.parametrize("rows", [4, 70])
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
 def test_mxfp4_activations_that_are_not_finite_are_never_served(rows, bad):
-    """An embedding with an infinity or a NaN: the six-bit parts hold neither, so their block
-    scales carry it, and the distribution is flagged as it is with bf16 weights."""
+    """An embedding with an infinity or a NaN: the distribution is flagged as it is with bf16
+    weights."""
     import torch
     import paper_2606_29565_amd as spp
     b = build_model(SMALL, 5, max_tokens=128)
@@ -230,3 +230,122 @@ def test_mxfp4_activations_that_are_not_finite_are_never_served(rows, bad):
     assert not torch.isfinite(dist).any()
     bitmap = torch.full(((SMALL.vocab + 31) // 32,), -1, dtype=torch.int32, device="cuda")
     assert spp.gate(r, 0.0, bitmap)[0] == spp.SPP_FALL_NONFINITE
+
+
+# ---- the activations' precision, element by element
+#
+# A model whose matrices are rows of unit vectors (code 2 is 1.0, scale byte 127 is 2^0), so
+# that every projection copies single elements of its input and the logits (an identity LM
+# head) are the residual stream times the final 1/RMS: what an activation lost on its way
+# into a projection shows in one logit.  One channel in 32 carries a norm gain of `ratio`, as
+# the outlier channels of trained models do; the others share its 32-element block.
+UNIT = synth.Shape("fp4unit", 1, 256, 4, 2, 64, 256, 256, 1e4, "bf16", wfmt="mxfp4")
+
+
+def _unit_rows(rows, cols, pick):
+    codes = np.zeros((rows, cols // 2), np.uint8)
+    for r, k in enumerate(pick):
+        codes[r, k // 2] |= 2 << (4 * (k & 1))
+    return codes
+
+
+def _unit_model(rows, gains, mats):
+    """UNIT with the given norm gains and the unit-vector picks of `mats` (other matrices 0)."""
+    import torch
+    b_w = synth.gpu_weights(UNIT, 1)
+    d = UNIT.d_model
+    rng = np.random.default_rng(11)
+    embed = torch.from_numpy(rng.standard_normal((UNIT.vocab, d)).astype(np.float32)).bfloat16().cuda()
+    b_w["embed"] = embed.reshape(-1).contiguous()
+    b_w["final_norm"] = torch.ones(d, dtype=torch.bfloat16, device="cuda")
+    b_w["lm_head"] = torch.eye(UNIT.vocab, d, dtype=torch.bfloat16, device="cuda").reshape(-1).contiguous()
+    for key in ("attn_norm", "mlp_norm"):
+        g = gains.get(key, np.ones(d, np.float32))
+        b_w[key] = [torch.from_numpy(g).bfloat16().cuda()]
+    kinds = {"wq": synth.WQ, "wk": synth.WK, "wv": synth.WV, "wo": synth.WO, "w_gate": synth.WG,
+             "w_up": synth.WU, "w_down": synth.WD}
+    for key, kind in kinds.items():
+        n, k = UNIT.weight_shape(kind)
+        pick = mats.get(key)
+        codes = _unit_rows(n, k, pick) if pick is not None else np.zeros((n, k // 2), np.uint8)
+        b_w[key] = [torch.from_numpy(codes).reshape(-1).cuda()]
+        b_w["scales"][key] = [torch.full((n * k // 32,), 127, dtype=torch.uint8, device="cuda")]
+    import paper_2606_29565_amd as spp
+    s = UNIT
+    m = spp.Model(s.n_layers, s.d_model, s.n_q, s.n_kv, s.head_dim, s.ffn, s.vocab, s.rope_base,
+                  s.bf16, b_w, rms_eps=s.eps, max_tokens=rows, mxfp4=True)
+    return m, embed.float().cpu().numpy().astype(np.float64)
+
+
+def _unit_run(m, rows, token):
+    import torch
+    import paper_2606_29565_amd as spp
+    sess = spp.Session(m, rows)
+    dist = torch.empty(UNIT.vocab, dtype=torch.float32, device="cuda")
+    sess.preposition([token] * rows, dist)
+    torch.cuda.synchronize()
+    return sess, dist.cpu().numpy().astype(np.float64)
+
+
+def _inv_rms(x):
+    return 1.0 / np.sqrt(np.mean(x * x) + UNIT.eps)
+
+
+# A projection input enters as it does with bf16 weights, as two bf16 halves, which leave at
+# most 2^-18 of an element whatever its neighbours are.
+HALVES = 2.0 ** -18
+FP32 = 2.0 ** -21   # the few fp32 roundings on the way from an element to its logit
+
+
+@pytest.mark.parametrize("rows", [1, 32, 33, 70])
+@pytest.mark.parametrize("ratio", [1.0, 128.0, 1024.0, 8192.0])
+def test_mxfp4_projection_inputs_keep_their_small_elements(rows, ratio):
+    """Gate/up and down inputs, the outliers in 1 of 32 channels of either."""
+    d, F, token = UNIT.d_model, UNIT.ffn, 3
+    rng = np.random.default_rng(5)
+    gain = np.ones(d, np.float32)
+    gain[7::32] = ratio
+    plain = np.array([c for c in range(d) if c % 32 != 7])
+    gate = rng.choice(plain, F)
+    up = rng.choice(plain, F)
+    up[5::32] = np.arange(7, d, 32)            # one SwiGLU output in 32 is an outlier
+    m, E = _unit_model(rows, {"mlp_norm": gain}, {"w_gate": gate, "w_up": up, "w_down": np.arange(d)})
+    sess, got = _unit_run(m, rows, token)
+    x0 = E[token]
+    y, inv = x0 * gain, _inv_rms(x0)
+    a, u = inv * y[gate], inv * y[up]
+    act = a / (1.0 + np.exp(-a)) * u
+    x = x0 + act
+    # relative error of one SwiGLU output: the gate's (d log silu / d log a <= 1 + |a|), the up's,
+    # the output's own
+    bound = (3.0 + np.abs(a)) * HALVES * np.abs(act) + FP32 * (np.abs(x0) + np.abs(act))
+    # (the final 1/RMS is common to all logits and follows the outliers' own error: the median
+    # of the ratios stands for it)
+    err = np.abs(got / np.median(got / x) - x)
+    log(f"unit model, {rows} rows, outliers {ratio:g}x: worst error {(err / bound).max():.3f} of its bound")
+    assert (err / bound).max() <= 1.0
+    sess.close()
+    m.close()
+
+
+@pytest.mark.parametrize("ratio", [1.0, 1024.0, 8192.0])
+def test_mxfp4_attention_output_keeps_its_small_elements(ratio):
+    """The O projection's input: with one key the attention output is the value cell itself."""
+    import paper_2606_29565_amd as spp
+    d, token = UNIT.d_model, 9
+    gain = np.ones(d, np.float32)
+    gain[7::32] = ratio
+    kv_rows = UNIT.n_kv * UNIT.head_dim
+    m, E = _unit_model(1, {"attn_norm": gain}, {"wv": np.arange(kv_rows), "wo": np.arange(d)})
+    sess, got = _unit_run(m, 1, token)
+    b = type("B", (), {"shape": UNIT, "model": m})
+    _, V = read_kv(b, sess, 0, 1)
+    head = np.arange(UNIT.n_q).repeat(UNIT.head_dim) // UNIT.group
+    att = V[head, 0, np.tile(np.arange(UNIT.head_dim), UNIT.n_q)].astype(np.float64)
+    x = E[token] + att
+    bound = HALVES * np.abs(att) + FP32 * (np.abs(E[token]) + np.abs(att))
+    err = np.abs(got / _inv_rms(x) - x)
+    log(f"unit model, attention output, outliers {ratio:g}x: worst error {(err / bound).max():.3f} of its bound")
+    assert (err / bound).max() <= 1.0
+    sess.close()
+    m.close()
