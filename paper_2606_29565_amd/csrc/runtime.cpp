@@ -115,6 +115,7 @@ struct Model {
   ScanResult* gate_host = nullptr;   // pinned, device-mapped [64] results, then the done word
   ScanResult* gate_dev = nullptr;
   uint32_t gate_seq = 0;
+  uint32_t gate_late = 0;            // a scan that its call gave up on and that may still run (0: none)
   DevBuf o_part, ml_part, params_dev;
   char* params_host = nullptr;
   size_t params_host_bytes = 0;
@@ -542,8 +543,37 @@ volatile uint32_t* gate_done_host(Model& m) {
 }
 uint32_t* gate_done_dev(Model& m) { return reinterpret_cast<uint32_t*>(m.gate_dev + k::kScanMax); }
 
+// The number of the model's next scan; 0 stands for none.
+uint32_t next_gate_seq(Model& m) {
+  if (++m.gate_seq == 0) ++m.gate_seq;
+  return m.gate_seq;
+}
+
+// How long a gate call waits for its scan.
+#ifndef SPP_GATE_WAIT_MS
+#define SPP_GATE_WAIT_MS 20000
+#endif
+
+// The gate's buffers, the arrival counters among them, are one scan's at a time.  A scan that its
+// call gave up on keeps them until it publishes its number (by then its counters are back at
+// zero): a scan beside it, on another stream, would count its arrivals too, and leave the
+// counters off zero for every gate after.  Waits for it as long as for a scan of one's own.
+// Caller holds m.gate_mu.
+spp_status gate_free(Model& m) {
+  if (!m.gate_late) return SPP_OK;
+  const auto t0 = std::chrono::steady_clock::now();
+  while (__atomic_load_n(gate_done_host(m), __ATOMIC_ACQUIRE) != m.gate_late) {
+    if (std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(SPP_GATE_WAIT_MS))
+      return fail(SPP_E_HIP, "an earlier gate scan of the model has not finished");
+    std::this_thread::yield();
+  }
+  m.gate_late = 0;
+  return SPP_OK;
+}
+
 // Waits until the scan has published `seq` in the done word (written after every result
 // of the batch is visible).  Falls back to the stream's completion; never waits forever.
+// Caller holds m.gate_mu.
 spp_status wait_done(Model& m, uint32_t seq, hipStream_t st) {
   volatile uint32_t* w = gate_done_host(m);
   const auto t0 = std::chrono::steady_clock::now();
@@ -556,8 +586,10 @@ spp_status wait_done(Model& m, uint32_t seq, hipStream_t st) {
         return fail(SPP_E_HIP, "gate scan finished without publishing its result");
       }
       if (q != hipErrorNotReady) return fail(SPP_E_HIP, "gate scan: %s", hipGetErrorString(q));
-      if (std::chrono::steady_clock::now() - t0 > std::chrono::seconds(20))
-        return fail(SPP_E_HIP, "gate scan did not finish within 20 s");
+      if (std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(SPP_GATE_WAIT_MS)) {
+        m.gate_late = seq;
+        return fail(SPP_E_HIP, "gate scan did not finish within %d ms", (int)SPP_GATE_WAIT_MS);
+      }
     }
   }
 }
@@ -1083,7 +1115,8 @@ spp_status spp_gate(spp_ready_t ready, float tau, const uint32_t* bitmap,
   Model& m = *s->m;
   hipSetDevice(m.device);
   std::lock_guard<std::mutex> gk(m.gate_mu);
-  const uint32_t seq = ++m.gate_seq;
+  if (const spp_status rc = gate_free(m); rc != SPP_OK) return rc;
+  const uint32_t seq = next_gate_seq(m);
   k::ScanJob job{};
   job.dist[0] = s->dist;
   job.bitmap[0] = bitmap;
@@ -1168,14 +1201,17 @@ spp_status gate_batch_impl(int32_t n, const spp_ready_t* ready, const float* tau
       job.with_lse = 0;
       if (where == GateScratch::kModel) {
         std::lock_guard<std::mutex> gk(m.gate_mu);
-        const uint32_t seq = ++m.gate_seq;
-        for (int j = 0; j < ns; ++j) job.result[j] = m.gate_dev + j;
-        job.parts = m.gate_parts;
-        job.done = gate_done_dev(m);
-        job.seq = seq;
-        const hipError_t e = k::scan(m.s, ns, job, st);
-        if (e != hipSuccess) rc = fail(SPP_E_HIP, "gate scan launch: %s", hipGetErrorString(e));
-        if (rc == SPP_OK) rc = wait_done(m, seq, st);
+        rc = gate_free(m);
+        if (rc == SPP_OK) {
+          const uint32_t seq = next_gate_seq(m);
+          for (int j = 0; j < ns; ++j) job.result[j] = m.gate_dev + j;
+          job.parts = m.gate_parts;
+          job.done = gate_done_dev(m);
+          job.seq = seq;
+          const hipError_t e = k::scan(m.s, ns, job, st);
+          if (e != hipSuccess) rc = fail(SPP_E_HIP, "gate scan launch: %s", hipGetErrorString(e));
+          if (rc == SPP_OK) rc = wait_done(m, seq, st);
+        }
         for (int j = 0; j < ns && rc == SPP_OK; ++j) res[j] = *const_cast<const ScanResult*>(m.gate_host + j);
       } else {
         // [kScanMax results][a scan buffer]; the results read back and every partial used

@@ -7,7 +7,9 @@
 //   3. the idle-window pass of Sec. 3.1 yielding to a flag set by another thread;
 //   4. gates of several sessions from several threads while another thread pre-positions,
 //      mutates and destroys sessions (the registry keeps a gated session alive);
-//   5. the batched pre-position and gate, and the gate entry point that allocates nothing.
+//   5. the batched pre-position and gate, and the gate entry point that allocates nothing;
+//   6. a gate that gives up on a scan still queued: the model's gate buffers (their arrival
+//      counters among them) stay that scan's until it has published its result.
 // Prints "OK" and exits 0 when every check holds.
 #include <atomic>
 #include <chrono>
@@ -372,6 +374,39 @@ void batched(spp_model_t m, const uint32_t* set) {
   for (Sess* s : ss) delete s;
 }
 
+void late_scan(spp_model_t m, const uint32_t* set) {
+  Sess s(m, 256, 0);
+  const auto delta = tokens(20, 10), entry = tokens(12, 11);
+  CHECK(spp_kv_append_delta(s.h, delta.data(), 20, nullptr) == SPP_OK);
+  spp_ready_t r{};
+  CHECK(spp_preposition(s.h, entry.data(), 12, s.dist, set, nullptr, &r) == SPP_OK);
+  finished(r);
+  hipStream_t a = nullptr, b = nullptr;
+  hipStreamCreate(&a);
+  hipStreamCreate(&b);
+  std::atomic<bool> go{false};
+  stub::enqueue(a, [&go] {
+    while (!go.load()) std::this_thread::yield();
+  });
+  int32_t tok = -1;
+  spp_gate_outcome o = SPP_SERVED;
+  const float tau = 2.f;
+  stub::gate_wait_ms = 50;
+  CHECK(spp_gate(r, tau, set, nullptr, 0, a, &tok, &o, nullptr) == SPP_E_HIP);  // gives up
+  // the scan is still queued on a: no other may start, from whichever entry point
+  CHECK(spp_gate(r, tau, set, nullptr, 0, b, &tok, &o, nullptr) == SPP_E_HIP && tok == -1);
+  CHECK(spp_gate_batch(1, &r, &tau, &set, b, &tok, &o) == SPP_E_HIP && tok == -1);
+  stub::gate_wait_ms = 20000;
+  go = true;
+  CHECK(gate(r, set, nullptr, &tok, b) == SPP_SERVED && tok == 7);
+  CHECK(spp_gate_batch(1, &r, &tau, &set, a, &tok, &o) == SPP_OK && o == SPP_SERVED && tok == 7);
+  CHECK(stub::gate_overlaps.load() == 0);
+  hipStreamSynchronize(a);
+  hipStreamSynchronize(b);
+  hipStreamDestroy(a);
+  hipStreamDestroy(b);
+}
+
 }  // namespace
 
 int main() {
@@ -388,6 +423,7 @@ int main() {
     idle_yield(m, set);
     concurrent(m, set);
     batched(m, set);
+    late_scan(m, set);
     hipDeviceSynchronize();
     CHECK(spp_model_destroy(m) == SPP_OK);
     for (void* p : keep) hipFree(p);

@@ -8,6 +8,7 @@
 // from starting new work, which makes "the device has not finished yet" reproducible.
 #pragma once
 
+#include <atomic>
 #include <cstddef>
 #include <cstdint>
 #include <functional>
@@ -88,4 +89,8 @@ void hold(bool on);
 long live_allocations();
 // Stops every worker thread (end of the program).
 void shutdown();
+// How long a gate waits for its scan (the runtime is built with SPP_GATE_WAIT_MS naming it).
+extern std::atomic<int> gate_wait_ms;
+// Gate scans launched while another scan on the same buffers had not published its result.
+extern std::atomic<int> gate_overlaps;
 }  // namespace stub

@@ -119,6 +119,8 @@ void enqueue(hipStream_t st, std::function<void()> fn) {
   s->q.push_back(std::move(fn));
   s->cv.notify_one();
 }
+std::atomic<int> gate_wait_ms{20000};
+std::atomic<int> gate_overlaps{0};
 void hold(bool on) { g_hold.store(on, std::memory_order_release); }
 long live_allocations() {
   std::lock_guard<std::mutex> lk(g_alloc_mu);

@@ -14,6 +14,8 @@
 #include <cmath>
 #include <cstring>
 #include <limits>
+#include <map>
+#include <mutex>
 
 #include "kernels.hpp"
 
@@ -155,6 +157,12 @@ hipError_t final_norm_rows(const Shape&, const StepView&, int, const float*, con
 hipError_t scan(const Shape& s, int n, const ScanJob& job, hipStream_t st) {
   const int V = s.vocab;
   const ScanJob j = job;  // the runtime's job record may be reused after the launch
+  static std::mutex mu;
+  static std::map<const void*, int> open;  // gate scans not yet published, by their buffers
+  if (j.done) {
+    std::lock_guard<std::mutex> lk(mu);
+    if (open[j.parts]++) stub::gate_overlaps.fetch_add(1);
+  }
   stub::enqueue(st, [=] {
     for (int b = 0; b < n; ++b) {
       float* d = j.dist[b];
@@ -168,7 +176,11 @@ hipError_t scan(const Shape& s, int n, const ScanJob& job, hipStream_t st) {
       const uint32_t extra = j.flag_src[b] ? *j.flag_src[b] : 0u;
       summarize(d, V, j.bitmap[b], j.with_lse != 0, extra, j.result[b], j.seq);
     }
-    if (j.done) __atomic_store_n(j.done, j.seq, __ATOMIC_RELEASE);
+    if (j.done) {
+      std::lock_guard<std::mutex> lk(mu);
+      --open[j.parts];
+      __atomic_store_n(j.done, j.seq, __ATOMIC_RELEASE);
+    }
   });
   return hipSuccess;
 }

@@ -4,7 +4,7 @@ for HIP and the kernels (tests/cpu_runtime/), and run under AddressSanitizer (+ 
 and ThreadSanitizer.  The driver covers the session state machine (Sec. 3.6, Alg. 1),
 Alg. 2's gate while the pre-position is still pending, the idle pass of Sec. 3.1 yielding
 to a flag set by another thread, gates racing mutations and session destruction, and the
-batched and allocation-free gates.  A last test plants an unsynchronized read of the
+batched and allocation-free gates, and a gate giving up on a scan still queued.  A last test plants an unsynchronized read of the
 yield flag in a copy of the runtime and checks that ThreadSanitizer reports it."""
 import os
 import shutil
@@ -25,6 +25,7 @@ pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not ava
 
 def _build(out, flags, runtime=RUNTIME):
     cmd = ["g++", "-std=c++17", "-O1", "-g", *flags, "-I", STUB,
+           "-DSPP_GATE_WAIT_MS=stub::gate_wait_ms",
            "-I", os.path.join(ROOT, "include"), "-I", CSRC, runtime, *OTHERS, "-o", out,
            "-lpthread"]
     r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
