@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "kernels.hpp"
+#include "plans.hpp"
 
 using namespace spp;
 
@@ -401,20 +402,13 @@ spp_status run_step(Model& m, const SegReq* segs, int nseg, bool logits, hipStre
   // h holds y = x * g of the next projection (RMSNorm factored; see k::res_blocks)
   LAUNCH(KC_EMBED, k::embed(s, dp, M, m.embed, m.attn_norm[0], m.x, m.h, h_lo, m.ss, m.rope, m.range,
                             st));
-  const auto plan = m.fp4 ? k::gemm_plan_fp4 : k::gemm_plan;
   const auto gemm = m.fp4 ? k::gemm_fp4 : k::gemm;
-  const k::GemmPlan p_qkv = plan(s, M, nq + 2 * nkv, d);
-  const k::GemmPlan p_o = plan(s, M, d, nq);
-  const k::GemmPlan p_gu = plan(s, M, 2 * F, d);
-  // gate/up with the SwiGLU fused (no K-splits), where it applies
-  const k::GemmPlan p_sw = m.fp4 ? k::gemm_plan_swiglu_fp4(s, M, F, d) : k::gemm_plan_swiglu(s, M, F, d);
   const auto gemm_sw = m.fp4 ? k::gemm_swiglu_fp4 : k::gemm_swiglu;
-  const k::GemmPlan p_dn = plan(s, M, d, F);
+  const StepPlans plans = step_plans(s, m.fp4, M);
+  const k::GemmPlan &p_qkv = plans.qkv, &p_o = plans.o, &p_sw = plans.sw, &p_gu = plans.gu, &p_dn = plans.dn;
   // every projection's split-K partials must fit the buffer sized at model creation
-  for (const auto& pn : {std::make_pair(p_qkv, nq + 2 * nkv), std::make_pair(p_o, d),
-                         std::make_pair(p_gu, 2 * F), std::make_pair(p_dn, d)})
-    if ((size_t)pn.first.splits * M * pn.second > m.part_elems)
-      return fail(SPP_E_INVALID_ARG, "partials of %d x %d rows exceed the work buffer", M, pn.second);
+  if (partial_elems(s, plans, M) > m.part_elems)
+    return fail(SPP_E_INVALID_ARG, "partials of %d rows exceed the work buffer", M);
   auto sc = [&](int kind, int l) -> const void* { return m.fp4 ? m.wsc[kind][l] : nullptr; };
   for (int l = 0; l < s.n_layers; ++l) {
     if (y && l > 0 && l % y->chunk == 0) {
@@ -745,21 +739,12 @@ spp_status spp_model_create(const spp_model_config* cfg, const spp_weights* w, s
   const Shape& s = m->s;
   const int nq = s.n_q * s.dh, nkv = s.n_kv * s.dh;
   const size_t Mx = (size_t)c.max_tokens;
-  // split-K partials: the largest of every projection's plan at every row count up to
-  // max_tokens (the split count falls with the row count in places, so no single row
-  // count bounds the product)
-  size_t part_elems = 0;
-  for (int M = 1; M <= c.max_tokens; ++M) {
-    const int shapes[4][2] = {{nq + 2 * nkv, s.d}, {s.d, nq}, {2 * s.ffn, s.d}, {s.d, s.ffn}};
-    for (auto& sh : shapes)
-      part_elems = std::max(part_elems, (size_t)(m->fp4 ? k::gemm_plan_fp4 : k::gemm_plan)(
-                                                    s, M, sh[0], sh[1]).splits * M * sh[0]);
-  }
-  m->part_elems = part_elems;
-  // batched LM head partials: the largest split count at any session count
+  m->part_elems = partial_elems_upto(s, m->fp4, c.max_tokens);
+  // batched LM head partials: the largest split count at any session count (the plan follows
+  // the row tiles: up to 16, 32 and 64 rows)
   int lm_splits = 1;
-  for (int n = 2; n <= c.max_sessions; ++n)
-    lm_splits = std::max(lm_splits, k::gemm_plan(s, n, s.vocab, s.d).splits);
+  for (int n : {2, 17, 33})
+    if (n <= c.max_sessions) lm_splits = std::max(lm_splits, k::gemm_plan(s, n, s.vocab, s.d).splits);
   bool ok = true;
   auto dmal = [&](void** p, size_t b) {
     if (ok && hipMalloc(p, b) != hipSuccess) ok = false;
@@ -769,7 +754,7 @@ spp_status spp_model_create(const spp_model_config* cfg, const spp_weights* w, s
   dmal(&m->q, 2 * Mx * nq * m->elem);       // hi, lo
   dmal(&m->att, 2 * Mx * nq * m->elem);     // hi, lo
   dmal(&m->act, 2 * Mx * s.ffn * m->elem);  // hi, lo
-  dmal((void**)&m->part, part_elems * 4);
+  dmal((void**)&m->part, m->part_elems * 4);
   dmal((void**)&m->ss, Mx * k::res_blocks(s) * 4);
   dmal((void**)&m->range, kMaxSegments * sizeof(uint32_t));
   dmal((void**)&m->rope, Mx * (s.dh / 2) * sizeof(float2));
