@@ -111,8 +111,8 @@ struct Model {
   float2* rope = nullptr;
   void* z = nullptr;
   float* logits_rows = nullptr;
-  ScanPartial* lm_parts = nullptr;   // buffers of k::kScanBufBytes
-  ScanPartial* gate_parts = nullptr;
+  ScanPartial* gate_parts = nullptr; // scan buffers of k::kScanBufBytes, one allocation
+  ScanPartial* lm_parts = nullptr;
   ScanResult* gate_host = nullptr;   // pinned, device-mapped [64] results, then the done word
   ScanResult* gate_dev = nullptr;
   uint32_t gate_seq = 0;
@@ -807,15 +807,10 @@ spp_status spp_model_create(const spp_model_config* cfg, const spp_weights* w, s
       }
     }
   }
-  dmal((void**)&m->lm_parts, k::kScanBufBytes);
-  dmal((void**)&m->gate_parts, k::kScanBufBytes);
-  // The arrival counters start at zero.  The copies are done when the device is waited for below
-  // (two blocking ones took about 100 us); only batches scan over lm_parts.
-  static const ScanPartial zeros[k::kScanCounters] = {};
-  for (ScanPartial* p : {m->gate_parts, c.max_sessions > 1 ? m->lm_parts : nullptr})
-    if (ok && p && hipMemcpyAsync(p + k::kScanParts, zeros, sizeof(zeros), hipMemcpyHostToDevice, nullptr) !=
-                       hipSuccess)
-      ok = false;
+  dmal((void**)&m->gate_parts, 2 * k::kScanBufBytes);
+  if (ok) m->lm_parts = m->gate_parts + k::kScanBufBytes / sizeof(ScanPartial);
+  // the arrival counters start at zero (done when the device is waited for below)
+  if (ok && k::clear_scan_counters(m->gate_parts, 2, nullptr) != hipSuccess) ok = false;
   if (ok && hipHostMalloc((void**)&m->gate_host, (k::kScanMax + 1) * sizeof(ScanResult),
                           hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
     ok = false;
@@ -838,7 +833,7 @@ spp_status spp_model_destroy(spp_model_t m) {
   if (!m) return SPP_OK;
   hipDeviceSynchronize();
   void* bufs[] = {m->x, m->h, m->q, m->att, m->act, m->part, m->rope, m->z, m->logits_rows,
-                  m->lm_parts, m->gate_parts, m->o_part.p,
+                  m->gate_parts, m->o_part.p,
                   m->ml_part.p, m->params_dev.p, m->lm_tiled, m->ss, m->range};
   for (void* p : bufs)
     if (p) hipFree(p);

@@ -287,6 +287,12 @@ __global__ __launch_bounds__(256) void lmhead_merge_kernel(const ScanPartial* pa
   if (threadIdx.x == 0) *result = make_result<true>(a, bitmap, range ? *range : 0u, 1u);
 }
 
+__global__ __launch_bounds__(256) void clear_counters_kernel(ScanPartial* bufs) {
+  ScanPartial* b = bufs + blockIdx.x * (k::kScanBufBytes / sizeof(ScanPartial)) + k::kScanParts;
+  for (int i = threadIdx.x; i < k::kScanCounters * 2; i += 256)
+    reinterpret_cast<uint4*>(b)[i] = make_uint4(0, 0, 0, 0);
+}
+
 // What one distribution of a scan needs, from the batch's job or from a job of one (whose
 // argument block is 25 times smaller: the workgroups read it from host memory).
 struct ScanJob1 {
@@ -507,6 +513,12 @@ int scan_blocks(int vocab, int n) {
   int nb, tpb;
   scan_launch(vocab, n, &nb, &tpb);
   return nb;
+}
+
+hipError_t clear_scan_counters(ScanPartial* bufs, int n, hipStream_t st) {
+  static_assert(kScanBufBytes % sizeof(ScanPartial) == 0 && sizeof(ScanPartial) == 32, "whole partials");
+  SPP_LAUNCH(clear_counters_kernel, dim3(n), dim3(256), 0, st, bufs);
+  return hipGetLastError();
 }
 
 hipError_t scan(const Shape& s, int n, const ScanJob& job, hipStream_t st) {

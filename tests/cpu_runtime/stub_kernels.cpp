@@ -154,6 +154,7 @@ hipError_t final_norm_rows(const Shape&, const StepView&, int, const float*, con
                            void*, hipStream_t st) {
   return nothing(st);
 }
+hipError_t clear_scan_counters(ScanPartial*, int, hipStream_t st) { return nothing(st); }
 hipError_t scan(const Shape& s, int n, const ScanJob& job, hipStream_t st) {
   const int V = s.vocab;
   const ScanJob j = job;  // the runtime's job record may be reused after the launch
