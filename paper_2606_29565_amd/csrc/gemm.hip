@@ -456,7 +456,8 @@ namespace k {
 //     (256) with at least two pipelined slices per workgroup: a second wave of
 //     workgroups, or shorter pipelines, cost more than the idle CUs.
 GemmPlan gemm_plan(const Shape& s, int M, int N, int K) {
-  if (tiled(s, M, N) && (M <= 256 || M > kTileMixRows)) return gemm_plan_tile(M, N, K, true);
+  const bool narrow = tiled(s, M, N) && N < kTileWide;
+  if (tiled(s, M, N) && !narrow && (M <= 256 || M > kTileMixRows)) return gemm_plan_tile(M, N, K, true);
   GemmPlan p{};
   const int kstep = kStepBytes / (s.bf16 ? 2 : 4);
   const int ksteps = K / kstep;
@@ -520,8 +521,8 @@ GemmPlan gemm_plan(const Shape& s, int M, int N, int K) {
     return p;
   }
   if (M > 256) {
-    // many rows (fp32 and narrow bf16 projections, and up to kTileMixRows rows the wide ones
-    // where gemm_tile's plan is longer): every workgroup runs one 64-row tile over the
+    // many rows (fp32 and narrow bf16 projections, and those that tiled() names where
+    // gemm_tile's plan is longer): every workgroup runs one 64-row tile over the
     // K-range of its split instead of passes over all rows, so each weight byte is read
     // from HBM once per split and shared by the tiles through the XCD's L2; four column
     // blocks per wave make each activation fragment read from LDS feed four matrix-core
@@ -550,12 +551,11 @@ GemmPlan gemm_plan(const Shape& s, int M, int N, int K) {
     p.iters = ksteps / p.splits;
     if (tiled(s, M, N)) {
       // The shorter of the two plans: a CU takes 1.45 us per step for two of these tiles and
-      // 1.6 for one of 128 rows, and the partials pass at 6 TB/s (they stay in the memory-side
-      // cache at these sizes).  For QKV, O and down of the 8B shape at 300 rows both estimates
+      // 1.6 for one of 128 rows.  For QKV, O and down of the 8B shape at 300 rows both estimates
       // are within 7% of the times at the tile kernel, and the faster side is picked.
       const GemmPlan t = gemm_plan_tile(M, N, K, true);
       auto us = [&](int wgs, int round, int steps, double step_us, int splits) {
-        return (double)((wgs + round - 1) / round) * steps * step_us + (double)splits * M * N * 8.0 / 6.0e6;
+        return (double)((wgs + round - 1) / round) * steps * step_us + (double)splits * M * N * 8.0 / kPartialRate;
       };
       const double here = us(p.row_tiles * groups * p.splits, 512, p.iters, 1.45, p.splits);
       const double tile = us(t.row_tiles * groups * t.splits, 256, (ksteps + t.splits - 1) / t.splits, 1.6,
@@ -580,6 +580,7 @@ GemmPlan gemm_plan(const Shape& s, int M, int N, int K) {
     if (slices % sp == 0 && (sp == 1 || slices / sp >= 2) && sp * groups <= 256) best = sp;
   p.splits = best;
   p.iters = slices / best;
+  if (narrow && best * groups < 100) return gemm_plan_tile(M, N, K, true);
   return p;
 }
 
@@ -606,8 +607,20 @@ GemmPlan gemm_plan_swiglu(const Shape& s, int M, int F, int K) {
   GemmPlan p{};
   const int kstep = kStepBytes / (s.bf16 ? 2 : 4);
   const int ksteps = K / kstep;
-  if (tiled(s, M, 2 * F) && F % 16 == 0) return gemm_plan_tile(M, 2 * F, K, false);
-  if (M > 256 && s.bf16 && F % 128 == 0 && 64 * res_blocks(s) <= 256) {
+  const bool rows64 = M > 256 && s.bf16 && F % 128 == 0 && 64 * res_blocks(s) <= 256;
+  if (tiled(s, M, 2 * F) && F % 16 == 0) {
+    const int groups = (2 * F + 255) / 256, tiles = (M + 127) / 128, tiles64 = (M + 63) / 64;
+    // Past 256 rows: 64-row tiles where they are one workgroup per CU, or two and the 128-row
+    // ones no longer one (an XCD has 32 CUs and takes whole column groups): one layer's gate/up +
+    // SwiGLU, 128 / 64 rows: d 2048, F 5632 300 rows 62.7 / 54.9 us, 500 rows 64.9 / 69.8, 700 rows
+    // 101.9 / 114.2; d 4096, F 11008 300 rows 184 / 131; the 8B shape 300 rows 184 / 210.
+    const int xcd = (groups + 7) / 8 * tiles, xcd64 = (groups + 7) / 8 * tiles64;  // workgroups of an XCD
+    if (rows64 ? xcd64 > 64 || (xcd64 > 32 && xcd <= 32)
+               : tiles * groups >= kTileFused || gemm_plan_tile(M, 2 * F, K, true).splits == 1)
+      return gemm_plan_tile(M, 2 * F, K, false);
+    if (!rows64) return p;
+  }
+  if (rows64) {
     // many rows: the 64-row tiles of gemm_plan over the full K (the SwiGLU needs every
     // split's sum), gate and up column blocks on alternate waves as below
     p.mt = 4;

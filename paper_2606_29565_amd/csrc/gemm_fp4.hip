@@ -342,7 +342,9 @@ hipError_t gemm_fp4(const Shape& s, const GemmPlan& p, const void* X, const void
 // more than its SwiGLU launch.
 GemmPlan gemm_plan_swiglu_fp4(const Shape& s, int M, int F, int K) {
   (void)s;
-  if (M <= kFp4Stream || F % 16 || K % kFp4Step) return GemmPlan{};
+  if (M <= kFp4Stream || F % 16 || K % kFp4Step ||
+      ((M + 127) / 128 * ((2 * F + 255) / 256) < kTileFused && gemm_plan_tile(M, 2 * F, K, true).splits > 1))
+    return GemmPlan{};
   return gemm_plan_tile(M, 2 * F, K, false);
 }
 

@@ -300,7 +300,7 @@ hipError_t launch(const k::GemmPlan& p, const void* X, const void* Xlo, int M, i
 namespace k {
 
 // The K-split count whose estimated time is least: a CU takes 1.6 us per workgroup and step (one
-// workgroup alone, or two in turn), and the fp32 partials are written and read at 4 TB/s.
+// workgroup alone, or two in turn), and the fp32 partials pass at kPartialRate.
 // (8B down projection of 2467 rows, 1 to 6 splits: 670, 532, 495, 470, 528, 512 us.)
 GemmPlan gemm_plan_tile(int M, int N, int K, bool split) {
   GemmPlan p{};
@@ -311,7 +311,7 @@ GemmPlan gemm_plan_tile(int M, int N, int K, bool split) {
   for (int sp = 1; split && sp <= 8 && (sp == 1 || sp * 4 <= ksteps); ++sp) {
     const int64_t wgs = (int64_t)p.row_tiles * groups * sp;
     const double t = (double)((wgs + 255) / 256) * ((ksteps + sp - 1) / sp) * 1.6 +
-                     (double)sp * M * N * 8.0 / 4.0e6;
+                     (double)sp * M * N * 8.0 / kPartialRate;
     if (sp == 1 || t < best) {
       best = t;
       p.splits = sp;

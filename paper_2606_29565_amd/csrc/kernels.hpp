@@ -214,23 +214,33 @@ hipError_t gemm_swiglu(const Shape& s, const GemmPlan& p, const void* X, const v
                        hipStream_t st);
 int pack_slab_steps_gateup(const Shape& s, int F, int K);
 
-// The same two projections of bf16 models over more than kTileRows rows (row_tiles tiles of 128
-// rows; splits of whole K-steps, not all alike): gemm_plan, gemm_plan_swiglu, gemm and
-// gemm_swiglu pass them on.  split = false: no K-splits (the fused form).
+// The same two projections over more than kTileRows rows, of bf16 and (w.scale set) MXFP4 weights
+// (row_tiles tiles of 128 rows; splits of whole K-steps, not all alike): gemm_plan,
+// gemm_plan_swiglu, gemm and gemm_swiglu and their MXFP4 forms pass them on.  split = false: no
+// K-splits (the fused form).  A plan of this kernel has mt = 0.
 //
-// Only projections at least kTileCols wide: those of the 8B and 32B shapes (N >= 4096; times at
-// the kernel).  With the d = 256 model (N <= 1024) the tiles leave most of the chip idle (4
-// layers, 153 rows: 314 -> 333 us; 30 sessions of up to 44 rows, 1 layer: 255 -> 262), so it
-// keeps the plans of gemm.hip.  Between the two widths nothing was measured.
+// For bf16 weights only projections at least kTileCols wide: with the d = 256 model (N <= 1024)
+// the tiles leave most of the chip idle (4 layers, 153 rows: 314 -> 333 us; 30 sessions of up to 44
+// rows, 1 layer: 255 -> 262), so it keeps the plans of gemm.hip.  From kTileWide on (the 8B and
+// 32B shapes) they always take the tiles, but from 257 to kTileMixRows rows, where three tiles
+// pad to 384 and five of 64 rows to 320: there the shorter of the two kernels' estimates decides
+// (the 8B QKV, the 32B QKV, O and down change; 8B 257 rows over 2 layers 809 -> 798 us, 32B 270 rows
+// 1548 -> 1501; beyond it gained nothing).  Between the two widths the estimates decide past 256
+// rows, and up to 256 the tiles take what the plans of gemm.hip leave under 100 workgroups.  us per
+// append over 4 layers, former plans / tiles always / now: d 2048 (F 5632) 129 rows 534 / 626 /
+// 530, 500 rows 756 / 757 / 725, 1000 rows 1271 / 1120 / 1118; d 1600 (F 4288, whose K-steps hardly
+// divide) 129 rows 1271 / 529 / 453, 1000 rows 1246 / 907 / 893; d 1024 (F 2816) 129 rows 374 / 425 /
+// 389, 400 rows 440 / 464 / 442.
 //
-// From 257 to kTileMixRows rows, where three of its tiles pad to 384 and five of 64 rows to 320,
-// gemm_plan takes the 64-row tiles of gemm.hip for the projections where their estimate is
-// shorter (the 8B QKV; the 32B QKV, O and down).  Appends over 2 layers, 128-row tiles alone and
-// now, one box: 8B 257 rows 809 -> 798 us, 300 817 -> 810; 32B 270 rows 1548 -> 1501, 300
-// 1559 -> 1533.  The same rule beyond gained nothing (8B 350: 843 -> 847, 700: 1376 -> 1404, 1000:
-// 1767 -> 1752; 32B 500: 2080 -> 2085, 900: 3728 -> 3753).
-// A plan of this kernel has mt = 0.
-constexpr int kTileRows = 128, kTileCols = 1536, kTileMixRows = 320;
+// The fused gate/up has no K-splits, so with few workgroups it is one long chain: under
+// kTileFused workgroups the projection is split instead and the SwiGLU a launch of its own (one
+// layer of d 2048, F 8192, 129 rows: 128 workgroups 62 us, unfused 47; d 1600, F 4288, 500 rows: 136
+// workgroups, 4 layers 643, unfused 677).
+constexpr int kTileRows = 128, kTileCols = 1536, kTileWide = 4096, kTileMixRows = 320, kTileFused = 130;
+// Bytes of partials written and read per us (they stay in the memory-side cache at these sizes):
+// what the planners charge.  At a copy's 4 TB/s the tiles took fewer splits: 8B 1000 rows 1742 ->
+// 1763 us, d 2048 300 rows 650 -> 676, 32B 640 rows 1425 -> 1404, the rest within 1%.
+constexpr double kPartialRate = 6.0e6;
 inline bool tiled(const Shape& s, int M, int N) { return s.bf16 && M > kTileRows && N >= kTileCols; }
 GemmPlan gemm_plan_tile(int M, int N, int K, bool split);
 hipError_t gemm_tile(const GemmPlan& p, const void* X, const void* Xlo, int M, int K,

@@ -545,14 +545,27 @@ def test_stream8b_full_model_every_logit_and_gate():
     assert decided >= 3 and any(o == spp.SPP_SERVED for o, _ in outcomes.values())
 
 
-@pytest.mark.parametrize("rows", [129, 144, 160, 255, 256, 257, 320, 321, 400])
-def test_many_row_projection_tiles_at_their_edges(rows):
-    """The 128-row, 256-column tiles of bf16 projections: a tile of one row, a partly filled wave
-    and a full one, odd numbers of K-steps (d = 1600: 25 of 64, F = 832: 13), widths that are no
-    whole tiles, several matrices per tile (Q, K and V): logits and cells against the oracle."""
+# d, query heads, kv heads, head_dim, F.  "split": odd numbers of K-steps (25 and 13 of 64), tiles
+# with K-splits, gate/up split with its own SwiGLU.  "fused": the SwiGLU fused over 25 steps, 131
+# column groups of 64 pairs (a partly filled last one).  "short": fused over 4 steps.  "rows64": past
+# 256 rows the fused 64-row tiles.  "narrow": O and down by the plans of gemm.hip up to 256 rows.
+TILE_SHAPES = {"split": (1600, 25, 5, 64, 832), "fused": (1600, 5, 5, 64, 8384), "short": (256, 4, 2, 64, 832),
+               "rows64": (512, 8, 2, 64, 1408), "narrow": (2048, 16, 4, 128, 1024)}
+
+
+@pytest.mark.parametrize("name,rows", [("split", r) for r in (129, 144, 160, 255, 256, 257, 320, 321, 400)] +
+                         [("fused", r) for r in (129, 256, 321)] +
+                         [("short", r) for r in (129, 300, 1100)] +
+                         [("rows64", r) for r in (256, 257, 400)] + [("narrow", r) for r in (129, 256, 400)])
+def test_many_row_projection_tiles_at_their_edges(name, rows):
+    """The 128-row, 256-column tiles of bf16 projections and the plans beside them: a tile of one
+    row, a partly filled wave and a full one, a second band of row tiles (more than 1024 rows),
+    widths that are no whole tiles, several matrices per tile (Q, K and V): logits and cells
+    against the oracle."""
     import torch
     import paper_2606_29565_amd as spp
-    shape = synth.Shape("tileedge", 1, 1600, 25, 5, 64, 832, 2048, 1e4, "bf16")
+    d, n_q, n_kv, dh, F = TILE_SHAPES[name]
+    shape = synth.Shape("tileedge", 1, d, n_q, n_kv, dh, F, 2048, 1e4, "bf16")
     seed = 91
     b = build_model(shape, seed, max_tokens=rows)
     toks = synth.cpu_tokens(rows, seed, 0, shape.vocab).tolist()
@@ -563,7 +576,7 @@ def test_many_row_projection_tiles_at_their_edges(rows):
     kvs = []
     ref = oracle_logits(shape, seed, 0, toks, kv_out=kvs)
     err = max_abs(dist.cpu().numpy(), ref)
-    log(f"many-row tiles, {rows} rows: max|dlogit| {err:.2e}")
+    log(f"many-row tiles, {name}, {rows} rows: max|dlogit| {err:.2e}")
     assert err <= LOGIT_TOL
     for l in range(shape.n_layers):
         K, V = read_kv(b, sess, l, rows)
