@@ -127,9 +127,8 @@ def test_70b_mxfp4_layer_full_width_matches_oracle():
 
 @pytest.mark.parametrize("n_past,L", [(100, 3), (70, 65), (33, 1)])
 def test_mxfp4_row_counts_of_every_launch_shape(n_past, L):
-    """Prefill rows of 100 / 70 / 33 (the split-K gate/up with the separate SwiGLU past 64
-    rows; 64-row tiles; 48-row tiles) and entries of 3, 65 and 1 rows against the
-    oracle, logits and every cache cell."""
+    """Prefill rows of 100 / 70 / 33 and entries of 3, 65 and 1 rows (the streaming kernel with
+    16, 64 and 128 rows) against the oracle, logits and every cache cell."""
     import torch
     import paper_2606_29565_amd as spp
     seed = 71
@@ -154,16 +153,16 @@ def test_mxfp4_row_counts_of_every_launch_shape(n_past, L):
 
 @pytest.mark.parametrize("packed", [False, True])
 def test_mxfp4_wide_mlp_four_column_blocks(packed):
-    """A 4-bit MLP as wide as 2 x 16384 outputs at 24 rows takes the unfused gate/up with
-    four column blocks per wave (then the separate SwiGLU); 12 rows keep the fused kernel.
-    Both against the oracle, logits and every cache cell, with the library packing its
-    own copies or handed tiled ones."""
+    """A 4-bit MLP as wide as 2 x 16384 outputs: four column blocks per wave at up to 64 rows
+    (then the separate SwiGLU), two at 65-128, the tile kernel with the SwiGLU fused at 150.
+    All against the oracle, logits and every cache cell, with the library packing its own
+    copies or handed tiled ones."""
     import torch
     import paper_2606_29565_amd as spp
     shape = synth.Shape("fp4wide", 1, 256, 4, 2, 64, 16384, 2048, 1e4, "bf16", wfmt="mxfp4")
     seed = 73
-    b = build_model(shape, seed, max_tokens=64, packed=packed)
-    for n_past, L in ((40, 24), (30, 12)):
+    b = build_model(shape, seed, max_tokens=150, packed=packed)
+    for n_past, L in ((40, 24), (30, 12), (20, 60), (10, 100), (20, 150)):
         toks = synth.cpu_tokens(n_past + L, seed, n_past, shape.vocab).tolist()
         sess = spp.Session(b.model, n_past + L + 8)
         sess.append_delta(toks[:n_past])
@@ -183,14 +182,24 @@ def test_mxfp4_wide_mlp_four_column_blocks(packed):
     b.model.close()
 
 
-@pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 64, 65, 127, 128, 129, 272])
-def test_mxfp4_rows_at_the_edges_of_the_projection_tiles(rows):
-    """Every edge of the row tiles (16, 32 and 64 rows of the streaming kernel, 128 of the tile
-    kernel), with an odd number of K-steps (F = 384: 3 of 128), matrices narrower than a
-    workgroup's columns, and heads of 64 dims: logits and cells against the oracle."""
+# layers, d, query heads, kv heads, head_dim, F.  "small": an odd number of K-steps (F = 384: 3 of
+# 128), matrices narrower than a workgroup's columns, heads of 64 dims.  "long": 15 and 13 steps, so
+# K-splits of unequal ranges that begin inside a slab (3 steps, for O) and turn the tile kernel's
+# buffers many times.  "fused": past 128 rows the SwiGLU fused over 15 steps.
+EDGE_SHAPES = {"small": (2, 256, 4, 2, 64, 384), "long": (1, 1920, 15, 1, 128, 1664),
+               "fused": (1, 1920, 15, 1, 128, 8320)}
+
+
+@pytest.mark.parametrize("name,rows",
+                         [("small", r) for r in (1, 16, 17, 32, 33, 64, 65, 127, 128, 129, 272, 1100)] +
+                         [("long", r) for r in (1, 24, 48, 65, 129, 300)] + [("fused", r) for r in (129, 300)])
+def test_mxfp4_rows_at_the_edges_of_the_projection_tiles(name, rows):
+    """Every edge of the row tiles (16, 32, 64 and 128 rows of the streaming kernel, 128 of the
+    tile kernel, whose second band begins at 1025 rows): logits and cells against the oracle."""
     import torch
     import paper_2606_29565_amd as spp
-    shape = synth.Shape("fp4edge", 2, 256, 4, 2, 64, 384, 2048, 1e4, "bf16", wfmt="mxfp4")
+    layers, d, n_q, n_kv, dh, F = EDGE_SHAPES[name]
+    shape = synth.Shape("fp4edge", layers, d, n_q, n_kv, dh, F, 2048, 1e4, "bf16", wfmt="mxfp4")
     seed = 77
     b = build_model(shape, seed, max_tokens=rows)
     toks = synth.cpu_tokens(20 + rows, seed, 0, shape.vocab).tolist()
@@ -203,7 +212,7 @@ def test_mxfp4_rows_at_the_edges_of_the_projection_tiles(rows):
     kvs = []
     ref = oracle_logits(shape, seed, 20, toks[20:], prefill=toks[:20], kv_out=kvs)
     err = max_abs(dist.cpu().numpy(), ref)
-    log(f"mxfp4 edges, {rows} rows: max|dlogit| {err:.2e}")
+    log(f"mxfp4 edges, {name}, {rows} rows: max|dlogit| {err:.2e}")
     assert err <= TOL
     for l in range(shape.n_layers):
         K, V = read_kv(b, sess, l, 20 + rows)
@@ -297,7 +306,7 @@ HALVES = 2.0 ** -18
 FP32 = 2.0 ** -21   # the few fp32 roundings on the way from an element to its logit
 
 
-@pytest.mark.parametrize("rows", [1, 32, 33, 70])
+@pytest.mark.parametrize("rows", [1, 32, 33, 70, 130])
 @pytest.mark.parametrize("ratio", [1.0, 128.0, 1024.0, 8192.0])
 def test_mxfp4_projection_inputs_keep_their_small_elements(rows, ratio):
     """Gate/up and down inputs, the outliers in 1 of 32 channels of either."""
