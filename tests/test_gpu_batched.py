@@ -1,16 +1,17 @@
 """Batched idle-window pre-positioning at its real configuration: 64 sessions of the
 8B shape (d 4096, 32/8 heads of 128, SwiGLU 14336, vocab 128256; two layers), each with
 U[1024, 8192] synthetic resident cells and an entry of U[8, 64] tokens, packed into one
-pass through spp_preposition_batch (Alg. 1 per session).  Every logit of every session
-is compared with the oracle's pass over that session alone.  Also: a model whose
-max_sessions is smaller than the batch splits it into passes of at most max_sessions
-decision points, each distribution equal to the session's own pre-position."""
+pass through spp_preposition_batch (Alg. 1 per session).  Every logit of every session,
+and every cell of its entry, is compared with the oracle's pass over that session alone.
+Also: a model whose max_sessions is smaller than the batch splits it into passes of at
+most max_sessions decision points, each distribution equal to the session's own
+pre-position."""
 import numpy as np
 import pytest
 
 import oracle
 import synth
-from gpu_util import build_model, fill_synthetic_kv, log, max_abs
+from gpu_util import build_model, fill_synthetic_kv, log, max_abs, read_kv
 
 pytestmark = pytest.mark.gpu
 
@@ -42,6 +43,9 @@ def test_batched64_real_configuration_every_logit():
     assert all(r.status == spp.SPP_OK for r in readies)
     got = [d.cpu().numpy().astype(np.float64) for d in dists]
     summs = [spp.ready_summary(r) for r in readies]
+    # the entry cells that the pass wrote, of every layer: no logit sees most of the last layer's
+    cells = [[tuple(c[:, n:n + m] for c in read_kv(b, s, l, n + m)) for l in range(shape.n_layers)]
+             for s, (n, m) in zip(sessions, spec)]
     for s in sessions:
         s.close()
     b.model.close()
@@ -61,6 +65,11 @@ def test_batched64_real_configuration_every_logit():
         if s.gap > 0.1:
             assert summs[i].argmax == s.argmax, (i, summs[i].argmax, s.argmax)
         assert summs[i].position == n + m
+        for l in range(shape.n_layers):
+            for c, o in zip(cells[i][l], kv.layer(l)):
+                # one bf16 rounding of the cell apart, and the slack of the other cell comparisons
+                o = np.asarray(o)[:, n:n + m]
+                assert np.all(np.abs(c - o) <= 2.0 ** -7 * np.maximum(np.abs(c), np.abs(o)) + 8e-3), (i, l)
     log(f"batched8b: worst max|dlogit| over 64 sessions {worst:.2e}")
 
 
