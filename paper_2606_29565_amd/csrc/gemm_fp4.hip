@@ -102,11 +102,11 @@ struct StepWalk {
     pos = t * nslab + sl;
   }
   // (selects, not branches: the caller's loop body stays one block)
-  __device__ __forceinline__ void next(bool go = true) {
+  __device__ __forceinline__ void next() {
     const bool wrap = t + 1 == slab;
-    sl += go && wrap ? 1 : 0;
-    pos = go ? (wrap ? sl : pos + nslab) : pos;
-    t = go ? (wrap ? 0 : t + 1) : t;
+    sl += wrap ? 1 : 0;
+    pos = wrap ? sl : pos + nslab;
+    t = wrap ? 0 : t + 1;
   }
 };
 

@@ -139,7 +139,7 @@ struct WeightCat {
 
 // Result of a reduction over one distribution (32 bytes).
 struct ScanResult {
-  int32_t argmax, second;  // (second: not set by the kernels)
+  int32_t argmax, pad0;
   float top1, top2, lse;
   uint32_t flags;    // bit 0 nonfinite, bit 1 argmax in the bitmap, bit 2 the fp16
                      // attention saw an input beyond its range (see kRangeFlag)
@@ -347,7 +347,6 @@ struct ScanJob {
   int with_lse;
 };
 hipError_t scan(const Shape& s, int n, const ScanJob& job, hipStream_t st);
-int scan_blocks(int vocab, int n);
 
 // Sliding-window shift of a session's cells (every layer): cells [delta, delta + n_new)
 // move to [0, n_new), keys turned back by delta positions (RoPE), values unchanged.

@@ -1217,7 +1217,7 @@ spp_status gate_batch_impl(int32_t n, const spp_ready_t* ready, const float* tau
 
 }  // namespace
 
-// Static scratch of spp_gate_batch_noalloc: the results and first-phase partials of one
+// Static scratch of spp_gate_batch_noalloc: the results and the scan buffer of one
 // scan of at most kScanMax distributions.  Each device holds its own copy of this array
 // for the life of the process; host code takes its address per device through
 // hipGetSymbolAddress (the name itself is a host-side stand-in, not a device address).

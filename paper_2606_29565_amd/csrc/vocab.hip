@@ -156,7 +156,7 @@ __device__ __forceinline__ ScanResult make_result(const Acc& a, const uint32_t* 
     flags |= ((bitmap[a.t.i1 >> 5] >> (a.t.i1 & 31)) & 1u) << 1;
   flags |= range & kRangeFlag;
   const float lse = LSE && !a.nonfinite ? a.m + __logf(a.s) : __builtin_nanf("");
-  return ScanResult{a.t.i1, -1, a.t.v1, a.t.v2, lse, flags, seq, 0};
+  return ScanResult{a.t.i1, 0, a.t.v1, a.t.v2, lse, flags, seq, 0};
 }
 
 // FULL: d is a multiple of 64 * E, so every lane's chunks are in the row and the loads
@@ -347,8 +347,9 @@ struct ScanJobN {
 };
 
 // One launch: grid (blocks, distributions).  Block x of distribution b takes an equal share of
-// the vocabulary's 16-byte units (the last block also takes the scalar tail when vocab % 4 != 0),
-// all its loads in flight at once.  The last workgroup of a distribution merges its partials
+// the vocabulary's 16-byte units, 8 of a thread's loads in flight at once (which is all of them up
+// to 131072 values in 64 distributions); a vocabulary that is no multiple of 4 is read value by
+// value, one load per thread and trip.  The last workgroup of a distribution merges its partials
 // (lane l partial l, nb <= 64) in a fixed order, and the last of the batch writes all results
 // (lane b result b).  When they go to host memory (job.done), that one wave makes them visible
 // to the host (one system-scope fence, which writes back its L2) and publishes the batch's
@@ -370,8 +371,7 @@ __global__ __launch_bounds__(256) void scan_kernel(int V, J job) {
   if ((V & 3) == 0) {
     const int V4 = V >> 2;
     const int u0 = (int)((int64_t)blockIdx.x * V4 / nb), u1 = (int)((int64_t)(blockIdx.x + 1) * V4 / nb);
-    constexpr int IN = 8;  // loads in flight per thread: one round trip per block
-                           // (scan_launch gives a block at most ~8 units per thread)
+    constexpr int IN = 8;  // loads in flight per thread
     for (int u = u0 + tid; u < u1; u += IN * TPB) {
       float4 q[IN];
 #pragma unroll
@@ -507,12 +507,6 @@ void scan_launch(int vocab, int n, int* nb, int* tpb) {
   const int cap = (vocab + 4 * *tpb - 1) / (4 * *tpb);
   if (*nb > cap) *nb = cap;
   if (*nb < 1) *nb = 1;
-}
-
-int scan_blocks(int vocab, int n) {
-  int nb, tpb;
-  scan_launch(vocab, n, &nb, &tpb);
-  return nb;
 }
 
 hipError_t clear_scan_counters(ScanPartial* bufs, int n, hipStream_t st) {

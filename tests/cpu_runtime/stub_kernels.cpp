@@ -26,7 +26,6 @@ void summarize(const float* d, int V, const uint32_t* bitmap, bool lse, uint32_t
                ScanResult* out, uint32_t seq) {
   ScanResult r{};
   r.argmax = -1;
-  r.second = -1;
   r.top1 = -std::numeric_limits<float>::infinity();
   r.top2 = r.top1;
   bool nonfinite = false;
@@ -38,12 +37,10 @@ void summarize(const float* d, int V, const uint32_t* bitmap, bool lse, uint32_t
     }
     if (x > r.top1) {
       r.top2 = r.top1;
-      r.second = r.argmax;
       r.top1 = x;
       r.argmax = v;
     } else if (x > r.top2) {
       r.top2 = x;
-      r.second = v;
     }
   }
   if (lse) {
@@ -74,7 +71,6 @@ namespace k {
 
 int res_blocks(const Shape& s) { return (s.d + 1023) / 1024; }
 int lmhead_blocks(const Shape&) { return 256; }
-int scan_blocks(int, int n) { return std::max(4, std::min(64, 1024 / std::max(n, 1))); }
 
 GemmPlan gemm_plan(const Shape&, int, int, int) { return GemmPlan{4, 2, 1, 2, 1, 2, 0}; }
 GemmPlan gemm_plan_swiglu(const Shape&, int, int, int) { return GemmPlan{4, 2, 1, 2, 1, 2, 0}; }
