@@ -100,12 +100,16 @@ __global__ __launch_bounds__(256, 2) void tile_kernel(const bf16_t* __restrict__
 
   // Workgroup id goes to XCD id % 8, slot id / 8.  An XCD's consecutive slots take `band` row
   // tiles of one (split, column group) and then the next group: the activations of a band and
-  // the weights of a group are both shared in its L2.
+  // the weights of a group are both shared in its L2.  Bands are alike and have no empty slots: as
+  // 8 + 1 or 8 + 2 tiles, with the second band filled up by workgroups that returned, appends of
+  // 1025-1280 rows over 2 layers of the 8B shape took 2475-2700 us (1200 rows 2656; by the 64-row
+  // tiles 2406), now 2003-2192 (2181).
   const int slot = blockIdx.x >> 3, xcd = blockIdx.x & 7;
   const int octs = (splits * groups + 7) / 8, per_band = octs * band;
   const int rb = slot / per_band, in = slot - rb * per_band;
-  const int xy = in / band * 8 + xcd, tile_m = rb * band + in % band;
-  if (xy >= splits * groups || tile_m >= row_tiles) return;
+  const int rows = min(band, row_tiles - rb * band);  // row tiles of this band (the last may be short)
+  const int xy = in / rows * 8 + xcd, tile_m = rb * band + in % rows;
+  if (xy >= splits * groups) return;
   const int split = xy % splits, cgroup = xy / splits;
   // the stored blocks: one step each, or (MXFP4) two
   constexpr int SPB = Q4 ? kFp4Step / kStep : 1;
@@ -276,9 +280,9 @@ __global__ __launch_bounds__(256, 2) void tile_kernel(const bf16_t* __restrict__
 template <bool SW, bool Q4>
 hipError_t launch_t(const k::GemmPlan& p, const void* X, const void* Xlo, int M, int K, const WeightCat& w,
                     int N, float* P, const SwigluTile& so, hipStream_t st) {
-  const int groups = (N + 16 * CB - 1) / (16 * CB), band = std::min(p.row_tiles, 8);
-  const int bands = (p.row_tiles + band - 1) / band, octs = (p.splits * groups + 7) / 8;
-  SPP_LAUNCH((tile_kernel<SW, Q4>), dim3((unsigned)(bands * band * octs * 8)), dim3(256), 0, st,
+  const int groups = (N + 16 * CB - 1) / (16 * CB), octs = (p.splits * groups + 7) / 8;
+  const int bands = (p.row_tiles + 7) / 8, band = (p.row_tiles + bands - 1) / bands;
+  SPP_LAUNCH((tile_kernel<SW, Q4>), dim3((unsigned)(p.row_tiles * octs * 8)), dim3(256), 0, st,
              static_cast<const bf16_t*>(X), static_cast<const bf16_t*>(Xlo), M, K, w, N, P, so, p.splits,
              groups, p.row_tiles, band);
   return hipGetLastError();

@@ -557,11 +557,12 @@ TILE_SHAPES = {"split": (1600, 25, 5, 64, 832), "fused": (1600, 5, 5, 64, 8384),
 
 @pytest.mark.parametrize("name,rows", [("split", r) for r in (129, 144, 160, 255, 256, 257, 320, 321, 400)] +
                          [("fused", r) for r in (129, 256, 321)] +
-                         [("short", r) for r in (129, 300, 1100)] +
+                         [("short", r) for r in (129, 300, 1100, 2060)] +
                          [("rows64", r) for r in (256, 257, 400)] + [("narrow", r) for r in (129, 256, 400)])
 def test_many_row_projection_tiles_at_their_edges(name, rows):
     """The 128-row, 256-column tiles of bf16 projections and the plans beside them: a tile of one
-    row, a partly filled wave and a full one, a second band of row tiles (more than 1024 rows),
+    row, a partly filled wave and a full one, two and three bands of row tiles (of 5 and 4, 6, 6
+    and 5),
     widths that are no whole tiles, several matrices per tile (Q, K and V): logits and cells
     against the oracle."""
     import torch
