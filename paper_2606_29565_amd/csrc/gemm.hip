@@ -456,8 +456,7 @@ namespace k {
 //     (256) with at least two pipelined slices per workgroup: a second wave of
 //     workgroups, or shorter pipelines, cost more than the idle CUs.
 GemmPlan gemm_plan(const Shape& s, int M, int N, int K) {
-  const bool narrow = tiled(s, M, N) && N < kTileWide;
-  if (tiled(s, M, N) && !narrow && (M <= 256 || M > kTileMixRows)) return gemm_plan_tile(M, N, K, true);
+  if (tiled(s, M, N) && M <= 256 && N >= kTileWide) return gemm_plan_tile(M, N, K, true);
   GemmPlan p{};
   const int kstep = kStepBytes / (s.bf16 ? 2 : 4);
   const int ksteps = K / kstep;
@@ -550,17 +549,14 @@ GemmPlan gemm_plan(const Shape& s, int M, int N, int K) {
     }
     p.iters = ksteps / p.splits;
     if (tiled(s, M, N)) {
-      // The shorter of the two plans: a CU takes 1.45 us per step for two of these tiles and
-      // 1.6 for one of 128 rows.  For QKV, O and down of the 8B shape at 300 rows both estimates
-      // are within 7% of the times at the tile kernel, and the faster side is picked.
+      // The shorter of the two plans.  This kernel's time by its busiest CU as at tile_us, within
+      // 10% at the same sizes (one or two workgroups share a CU; more follow in turn).
+      const int busiest = ((groups * p.splits + 7) / 8 * p.row_tiles + 31) / 32;
+      const double here = (busiest == 1 ? 1.45 * p.iters : busiest * ((busiest == 2 ? 0.82 : 0.88) * p.iters + 1.5)) + 8;
       const GemmPlan t = gemm_plan_tile(M, N, K, true);
-      auto us = [&](int wgs, int round, int steps, double step_us, int splits) {
-        return (double)((wgs + round - 1) / round) * steps * step_us + (double)splits * M * N * 8.0 / kPartialRate;
-      };
-      const double here = us(p.row_tiles * groups * p.splits, 512, p.iters, 1.45, p.splits);
-      const double tile = us(t.row_tiles * groups * t.splits, 256, (ksteps + t.splits - 1) / t.splits, 1.6,
-                             t.splits);
-      if (tile <= here) return t;
+      const double tile = tile_us(t.row_tiles, groups, t.splits, (ksteps + t.splits - 1) / t.splits);
+      if (tile + (double)t.splits * M * N * 8.0 / kPartialRate <= here + (double)p.splits * M * N * 8.0 / kPartialRate)
+        return t;
     }
     return p;
   }
@@ -580,7 +576,7 @@ GemmPlan gemm_plan(const Shape& s, int M, int N, int K) {
     if (slices % sp == 0 && (sp == 1 || slices / sp >= 2) && sp * groups <= 256) best = sp;
   p.splits = best;
   p.iters = slices / best;
-  if (narrow && best * groups < 100) return gemm_plan_tile(M, N, K, true);
+  if (tiled(s, M, N) && best * groups < 100) return gemm_plan_tile(M, N, K, true);
   return p;
 }
 
@@ -609,13 +605,14 @@ GemmPlan gemm_plan_swiglu(const Shape& s, int M, int F, int K) {
   const int ksteps = K / kstep;
   const bool rows64 = M > 256 && s.bf16 && F % 128 == 0 && 64 * res_blocks(s) <= 256;
   if (tiled(s, M, 2 * F) && F % 16 == 0) {
+    // Past 256 rows the 64-row tiles where their time per step, by the busiest CU as at gemm_plan, is
+    // shorter: one layer's gate/up + SwiGLU with 128- / 64-row tiles, us: 8B 400 rows 205 / 235, 550
+    // rows 298 / 266, 640 rows 302 / 333, 1216 rows 526 / 573; d 4096, F 11008 300 rows 184 / 131, 700
+    // rows 306 / 259; d 2048, F 5632 300 rows 63 / 55, 500 rows 65 / 70; 32B within 2% throughout.
     const int groups = (2 * F + 255) / 256, tiles = (M + 127) / 128, tiles64 = (M + 63) / 64;
-    // Past 256 rows: 64-row tiles where they are one workgroup per CU, or two and the 128-row
-    // ones no longer one (an XCD has 32 CUs and takes whole column groups): one layer's gate/up +
-    // SwiGLU, 128 / 64 rows: d 2048, F 5632 300 rows 62.7 / 54.9 us, 500 rows 64.9 / 69.8, 700 rows
-    // 101.9 / 114.2; d 4096, F 11008 300 rows 184 / 131; the 8B shape 300 rows 184 / 210.
-    const int xcd = (groups + 7) / 8 * tiles, xcd64 = (groups + 7) / 8 * tiles64;  // workgroups of an XCD
-    if (rows64 ? xcd64 > 64 || (xcd64 > 32 && xcd <= 32)
+    const int c = ((groups + 7) / 8 * tiles + 31) / 32, c64 = ((groups + 7) / 8 * tiles64 + 31) / 32;
+    const double tile = c == 1 ? 1.95 : 1.6 * c, t64 = c64 == 1 ? 1.72 : (c64 == 2 ? 2.1 : 1.03 * c64 + 0.2);
+    if (rows64 ? tile <= t64
                : tiles * groups >= kTileFused || gemm_plan_tile(M, 2 * F, K, true).splits == 1)
       return gemm_plan_tile(M, 2 * F, K, false);
     if (!rows64) return p;

@@ -303,9 +303,17 @@ hipError_t launch(const k::GemmPlan& p, const void* X, const void* Xlo, int M, i
 
 namespace k {
 
-// The K-split count whose estimated time is least: a CU takes 1.6 us per workgroup and step (one
-// workgroup alone, or two in turn), and the fp32 partials pass at kPartialRate.
-// (8B down projection of 2467 rows, 1 to 6 splits: 670, 532, 495, 470, 528, 512 us.)
+// The time of the kernel, estimated from the workgroups that the busiest CU takes: an XCD gets
+// whole (split, column group) pairs, each with all the row tiles, and has 32 CUs.  Within 8% of
+// the QKV, O and down projections of the 8B and 32B shapes and of d = 4096, F = 11008 at 321 to 2000
+// rows; estimating from the chip's workgroups instead (32B down, 550 rows: 500 of them, but 65 on
+// some XCDs) had picked splits 20% slower than the best.
+double tile_us(int row_tiles, int groups, int splits, int steps) {
+  const int busiest = ((groups * splits + 7) / 8 * row_tiles + 31) / 32;
+  return busiest == 1 ? 1.95 * steps + 8.5 : busiest * (1.64 * steps + 3.5) + 5;
+}
+
+// The K-split count whose estimated time is least, with the fp32 partials at kPartialRate.
 GemmPlan gemm_plan_tile(int M, int N, int K, bool split) {
   GemmPlan p{};
   const int ksteps = K / kStep, groups = (N + 16 * CB - 1) / (16 * CB);
@@ -313,8 +321,7 @@ GemmPlan gemm_plan_tile(int M, int N, int K, bool split) {
   p.splits = p.iters = 1;
   double best = 0;
   for (int sp = 1; split && sp <= 8 && (sp == 1 || sp * 4 <= ksteps); ++sp) {
-    const int64_t wgs = (int64_t)p.row_tiles * groups * sp;
-    const double t = (double)((wgs + 255) / 256) * ((ksteps + sp - 1) / sp) * 1.6 +
+    const double t = tile_us(p.row_tiles, groups, sp, (ksteps + sp - 1) / sp) +
                      (double)sp * M * N * 8.0 / kPartialRate;
     if (sp == 1 || t < best) {
       best = t;

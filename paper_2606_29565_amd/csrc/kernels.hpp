@@ -221,28 +221,30 @@ int pack_slab_steps_gateup(const Shape& s, int F, int K);
 //
 // For bf16 weights only projections at least kTileCols wide: with the d = 256 model (N <= 1024)
 // the tiles leave most of the chip idle (4 layers, 153 rows: 314 -> 333 us; 30 sessions of up to 44
-// rows, 1 layer: 255 -> 262), so it keeps the plans of gemm.hip.  From kTileWide on (the 8B and
-// 32B shapes) they always take the tiles, but from 257 to kTileMixRows rows, where three tiles
-// pad to 384 and five of 64 rows to 320: there the shorter of the two kernels' estimates decides
-// (the 8B QKV, the 32B QKV, O and down change; 8B 257 rows over 2 layers 809 -> 798 us, 32B 270 rows
-// 1548 -> 1501; beyond it gained nothing).  Between the two widths the estimates decide past 256
-// rows, and up to 256 the tiles take what the plans of gemm.hip leave under 100 workgroups.  us per
-// append over 4 layers, former plans / tiles always / now: d 2048 (F 5632) 129 rows 534 / 626 /
-// 530, 500 rows 756 / 757 / 725, 1000 rows 1271 / 1120 / 1118; d 1600 (F 4288, whose K-steps hardly
-// divide) 129 rows 1271 / 529 / 453, 1000 rows 1246 / 907 / 893; d 1024 (F 2816) 129 rows 374 / 425 /
-// 389, 400 rows 440 / 464 / 442.
+// rows, 1 layer: 255 -> 262), and so it is with N = 1536 (QKV of d 1024, K of 16 steps: 11 -> 19 us
+// at 500 rows), so they keep the plans of gemm.hip.  Up to 256 rows the projections from
+// kTileWide on (the 8B and 32B shapes) take the tiles, narrower ones where the plans of gemm.hip
+// leave under 100 workgroups.  Past 256 rows the shorter of the two kernels' estimates decides
+// (gemm_plan).  us per append over 2 layers of the 8B shape, one layer of the 32B, 64-row tiles /
+// 128-row tiles (64-row ones by estimate up to 320 rows) / now: 8B 300 rows 870 / 803 / 798, 550 rows
+// 1152 / 1213 / 1135, 1000 rows 1836 / 1782 / 1735; 32B 400 rows 989 / 1021 / 994, 550 rows 1247 / 1367 /
+// 1236, 1200 rows 2489 / 2732 / 2346.  Narrower models over 4 layers, former plans / tiles always /
+// now: d 2048 (F 5632) 129 rows 535 / 628 / 529, 500 rows 745 / 759 / 738, 1000 rows 1262 / 1121 / 1116; d
+// 1600 (F 4288, whose K-steps hardly divide) 129 rows 1275 / 530 / 454, 1000 rows 1236 / 901 / 881; d
+// 1024 (F 2816) 129 rows 377 / 430 / 389, 500 rows 459 / 484 / 458, 2000 rows 998 / 841 / 897.
 //
 // The fused gate/up has no K-splits, so with few workgroups it is one long chain: under
 // kTileFused workgroups the projection is split instead and the SwiGLU a launch of its own (one
 // layer of d 2048, F 8192, 129 rows: 128 workgroups 62 us, unfused 47; d 1600, F 4288, 500 rows: 136
 // workgroups, 4 layers 643, unfused 677).
-constexpr int kTileRows = 128, kTileCols = 1536, kTileWide = 4096, kTileMixRows = 320, kTileFused = 130;
+constexpr int kTileRows = 128, kTileCols = 1600, kTileWide = 4096, kTileFused = 130;
 // Bytes of partials written and read per us (they stay in the memory-side cache at these sizes):
 // what the planners charge.  At a copy's 4 TB/s the tiles took fewer splits: 8B 1000 rows 1742 ->
 // 1763 us, d 2048 300 rows 650 -> 676, 32B 640 rows 1425 -> 1404, the rest within 1%.
 constexpr double kPartialRate = 6.0e6;
 inline bool tiled(const Shape& s, int M, int N) { return s.bf16 && M > kTileRows && N >= kTileCols; }
 GemmPlan gemm_plan_tile(int M, int N, int K, bool split);
+double tile_us(int row_tiles, int groups, int splits, int steps);  // estimated time
 hipError_t gemm_tile(const GemmPlan& p, const void* X, const void* Xlo, int M, int K,
                      const WeightCat& w, int N, float* partials, hipStream_t st);
 hipError_t gemm_tile_swiglu(const Shape& s, const GemmPlan& p, const void* X, const void* Xlo, int M,

@@ -35,13 +35,13 @@ inline size_t partial_elems(const Shape& s, const StepPlans& p, int M) {
 
 // Floats that hold the partials of every pass of up to max_rows rows.  The split counts do not
 // grow with the row count inside a bucket of the planners' row tiles (16, 32, then whole 64s):
-// the plans of a bucket's first row count, at its last one, bound the bucket.  Between 257 and
-// kTileMixRows rows the planner compares two kernels, so each count is asked.  (Asking every count
-// up to 8192 took 2 ms of a model's creation.)
+// the plans of a bucket's first row count, at its last one, bound the bucket (the planners charge
+// partials by the row, so a larger count turns only to fewer splits).  Asking every count up to 8192
+// took 2 ms of a model's creation.
 inline size_t partial_elems_upto(const Shape& s, bool fp4, int max_rows) {
   size_t most = 0;
   for (int lo = 1; lo <= max_rows;) {
-    const int hi = lo == 1 ? 16 : lo == 17 ? 32 : lo > 256 && lo <= k::kTileMixRows ? lo : (lo + 63) / 64 * 64;
+    const int hi = lo == 1 ? 16 : lo == 17 ? 32 : (lo + 63) / 64 * 64;
     most = std::max(most, partial_elems(s, step_plans(s, fp4, lo), std::min(hi, max_rows)));
     lo = hi + 1;
   }
