@@ -106,12 +106,13 @@ struct Model {
   void* act = nullptr;
   float* part = nullptr;
   size_t part_elems = 0;              // floats of `part`
+  char* small = nullptr;              // one allocation: the scan buffers, ss, range, rope and z
   float* ss = nullptr;                // row sums of squares [max_tokens][res_blocks]
   uint32_t* range = nullptr;          // the step's fp16 range word per segment [kMaxSegments]
   float2* rope = nullptr;
   void* z = nullptr;
   float* logits_rows = nullptr;
-  ScanPartial* gate_parts = nullptr; // scan buffers of k::kScanBufBytes, one allocation
+  ScanPartial* gate_parts = nullptr; // two scan buffers of k::kScanBufBytes, side by side
   ScanPartial* lm_parts = nullptr;
   ScanResult* gate_host = nullptr;   // pinned, device-mapped [64] results, then the done word
   ScanResult* gate_dev = nullptr;
@@ -755,10 +756,27 @@ spp_status spp_model_create(const spp_model_config* cfg, const spp_weights* w, s
   dmal(&m->att, 2 * Mx * nq * m->elem);     // hi, lo
   dmal(&m->act, 2 * Mx * s.ffn * m->elem);  // hi, lo
   dmal((void**)&m->part, m->part_elems * 4);
-  dmal((void**)&m->ss, Mx * k::res_blocks(s) * 4);
-  dmal((void**)&m->range, kMaxSegments * sizeof(uint32_t));
-  dmal((void**)&m->rope, Mx * (s.dh / 2) * sizeof(float2));
-  dmal(&m->z, 2 * (size_t)k::kScanMax * s.d * m->elem);  // hi, lo
+  {  // the smaller buffers share one allocation
+    size_t bytes = 0;
+    auto place = [&](size_t b) {
+      const size_t at = bytes;
+      bytes += (size_t)round_up((int64_t)b, 256);
+      return at;
+    };
+    const size_t o_scan = place(2 * k::kScanBufBytes), o_ss = place(Mx * k::res_blocks(s) * 4),
+                 o_range = place(kMaxSegments * sizeof(uint32_t)),
+                 o_rope = place(Mx * (s.dh / 2) * sizeof(float2)),
+                 o_z = place(2 * (size_t)k::kScanMax * s.d * m->elem);  // hi, lo
+    dmal((void**)&m->small, bytes);
+    if (ok) {
+      m->gate_parts = reinterpret_cast<ScanPartial*>(m->small + o_scan);
+      m->lm_parts = m->gate_parts + k::kScanBufBytes / sizeof(ScanPartial);
+      m->ss = reinterpret_cast<float*>(m->small + o_ss);
+      m->range = reinterpret_cast<uint32_t*>(m->small + o_range);
+      m->rope = reinterpret_cast<float2*>(m->small + o_rope);
+      m->z = m->small + o_z;
+    }
+  }
   if (c.max_sessions > 1) {
     dmal((void**)&m->logits_rows, (size_t)lm_splits * c.max_sessions * s.vocab * 4);
     dmal(&m->lm_tiled, (size_t)s.vocab * s.d * m->elem);
@@ -807,10 +825,6 @@ spp_status spp_model_create(const spp_model_config* cfg, const spp_weights* w, s
       }
     }
   }
-  dmal((void**)&m->gate_parts, 2 * k::kScanBufBytes);
-  if (ok) m->lm_parts = m->gate_parts + k::kScanBufBytes / sizeof(ScanPartial);
-  // the arrival counters start at zero (done when the device is waited for below)
-  if (ok && k::clear_scan_counters(m->gate_parts, 2, nullptr) != hipSuccess) ok = false;
   if (ok && hipHostMalloc((void**)&m->gate_host, (k::kScanMax + 1) * sizeof(ScanResult),
                           hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
     ok = false;
@@ -821,6 +835,12 @@ spp_status spp_model_create(const spp_model_config* cfg, const spp_weights* w, s
     if (hipEventCreateWithFlags(&m->chunk_end[i], hipEventDisableTiming) != hipSuccess) ok = false;
   if (ok) memset(m->gate_host, 0, (k::kScanMax + 1) * sizeof(ScanResult));
   if (ok && hipDeviceSynchronize() != hipSuccess) ok = false;
+  // The arrival counters start at zero: the model's first step orders after this as after a step
+  // (and a gate comes after a finished step).
+  if (ok && (k::clear_scan_counters(m->gate_parts, 2, nullptr) != hipSuccess ||
+             hipEventRecord(m->step_done, nullptr) != hipSuccess))
+    ok = false;
+  m->step_recorded = ok;
   if (!ok) {
     spp_model_destroy(m);
     return fail(SPP_E_NOMEM, "could not allocate the model work buffers");
@@ -832,9 +852,8 @@ spp_status spp_model_create(const spp_model_config* cfg, const spp_weights* w, s
 spp_status spp_model_destroy(spp_model_t m) {
   if (!m) return SPP_OK;
   hipDeviceSynchronize();
-  void* bufs[] = {m->x, m->h, m->q, m->att, m->act, m->part, m->rope, m->z, m->logits_rows,
-                  m->gate_parts, m->o_part.p,
-                  m->ml_part.p, m->params_dev.p, m->lm_tiled, m->ss, m->range};
+  void* bufs[] = {m->x, m->h, m->q, m->att, m->act, m->part, m->small, m->logits_rows,
+                  m->o_part.p, m->ml_part.p, m->params_dev.p, m->lm_tiled};
   for (void* p : bufs)
     if (p) hipFree(p);
   for (void* p : m->owned) hipFree(p);
