@@ -20,12 +20,12 @@
 //    300 rows    34.9 ->  45.3    31.7 ->  31.2    209.8 -> 184.4    92.3 ->  82.9
 //    203 rows    38.8 ->  32.0    28.2 ->  24.1    142.4 -> 112.8    67.4 ->  56.3
 // The larger tile leaves part of the chip idle where 128 x 256 divides badly (QKV at 300 and 1000
-// rows, down at 1000), which gate/up makes up for: the four together are 5-23% faster throughout.
-// At 257-320 rows gemm_plan takes the 64-row tiles where they are estimated shorter (QKV above).
+// rows, down at 1000): past 256 rows gemm_plan takes the 64-row tiles where they are estimated
+// shorter.
 // MXFP4 weights take the same tiles: a block of codes holds two steps, and the wave that brings
-// it in makes the bf16 operands on the way to LDS.  Appends over 3 layers of the 70B shape, us,
-// 128-row passes over all weights and now: 129 rows 2558 -> 2384, 300 rows 3998 -> 3331, 700 rows
-// 8216 -> 6428, 1100 rows 12615 -> 11485.
+// it in makes the bf16 operands on the way to LDS.  Appends over one layer of the 70B shape, us,
+// 128-row passes over all weights and now: 129 rows 865 -> 774, 300 rows 1343 -> 1132, 640 rows
+// 2353 -> 1865, 1100 rows 4246 -> 3248.
 // 128-column tiles (twice the activation traffic per product) took 1.2-1.4 times as long at 2467
 // rows.  At 128 rows and fewer the passes of gemm.hip stay ahead (128 rows: 166 us per layer, 174
 // with 128-column tiles, 204 with 256).
