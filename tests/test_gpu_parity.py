@@ -408,9 +408,9 @@ def test_stream8b_full_model_golden():
 
 
 def test_many_row_entry_full_depth_golden():
-    """300 entry rows on the 32-layer 8B model: past 256 rows every projection runs the
-    64-row-tile plans of the batched pass (hi and lo products, the fused gate/up), so
-    this pins those kernels over the full depth against the oracle's stored result."""
+    """300 entry rows on the 32-layer 8B model: past 256 rows the projections run 64- or 128-row
+    tiles, whichever is estimated shorter (hi and lo products, the fused gate/up), so this
+    pins those kernels over the full depth against the oracle's stored result."""
     torch, spp = _spp()
     with open(os.path.join(GOLDEN, "many_rows_8b_golden.json")) as f:
         g = json.load(f)
