@@ -346,7 +346,10 @@ spp_status spp_ready_summary(spp_ready_t ready, spp_summary* out);
  * words; NULL = empty set) -> SPP_FALL_NOT_IN_SET; else SPP_SERVED with
  * *token_out = argmax (otherwise *token_out = -1).  Synchronous.  Read-only: the
  * distribution keeps serving repeated requests.  SPP_E_INVALID_ARG for tau < 0 or
- * NaN.  `scan_out` (nullable) receives the scan's summary. */
+ * NaN; SPP_E_HIP if the scan has not finished after 20 s.  Until that scan has, the next
+ * gates of the model (spp_gate_batch too, on whatever stream) wait as long for it and
+ * return the same error, with no scan of their own.  `scan_out` (nullable) receives the
+ * scan's summary. */
 spp_status spp_gate(spp_ready_t ready, float tau, const uint32_t* fast_bitmap_dev,
                     const int32_t* realized_entry, int32_t n_realized, void* stream,
                     int32_t* token_out, spp_gate_outcome* outcome, spp_summary* scan_out);
